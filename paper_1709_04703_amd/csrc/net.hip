@@ -14,6 +14,7 @@
 // the channel roles swapped (BACKWARD flag); the weight gradient reduces
 // In^T * G over voxels on the matrix cores, per workgroup, then in a fixed
 // order over workgroups (deterministic).
+#include <algorithm>
 #include <cmath>
 
 #include "internal.h"
@@ -24,8 +25,12 @@ namespace {
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// 16 bytes from memory of the callers' own alignment (2 bytes for BF16
+// activations, 4 for FP32 scratch)
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
 constexpr int kNC = 16;                 // channels
-constexpr int kCTY = 4, kCTZ = 8;             // weight-gradient tile: 4 rows, 8 planes
 
 __device__ inline uint16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
@@ -171,81 +176,236 @@ k_conv(int n, const uint16_t* __restrict__ in, const float* __restrict__ w,
 
 // ---------------------------------------------------------- weight gradient
 // dW[t][ci][co] = sum_v in[v + off_t][ci] g[v][co]; db[co] = sum_v g[v][co].
-// MFMA: D (ci x co) += A (ci x 16 voxels) * B (16 voxels x co) with
-// A[ci = r][k = 4g + q] = in[v_k + off_t][ci], B[k][co = r] = g[v_k][co].
-// A workgroup covers gxw groups of 16 voxels in x, 4 rows, kCTZ planes; the
-// 4 waves' partials are summed in LDS and written per workgroup.
+// On the matrix cores with the voxels of a row as the contraction index:
+// D (ci x co) += A (ci x 32 voxels) * B (32 voxels x co), a lane's fragment
+// being 8 consecutive voxels of one channel.  Activations are channels-last,
+// so both operands are staged transposed in LDS ([row][channel][x]): a thread
+// loads 8 channels of two neighbouring voxels and writes 8 dwords.
+//
+// A workgroup of 8 waves takes a column of kWX voxels in x and 8 rows and
+// marches its planes; it owns the products whose g voxel lies in its x range
+// and whose input row is one of its rows (in: one voxel of halo in x; g: one
+// row and plane of halo in y and z).  Each wave owns one input row: it reads
+// the row's fragment once, forms its x +- 1 shifts in registers (a fragment
+// shifted by one 2-byte voxel is not aligned in LDS), and multiplies the
+// three with the fragments of the nine g rows that row pairs with.  g planes
+// sit in a ring of 4, input planes in a ring of 2, so one barrier per plane
+// separates writes from reads, and the next plane's global loads are in
+// flight during the products.  db is one more product, with A = 1.
+// Bound by the matrix cores and LDS reads (10.5 KB per 28 products).  Row
+// strides of 88 and 72 entries put the 16 channels of a fragment read on
+// distinct banks.  At 128^3 it takes 50 us (0.58 PFLOP/s); with one
+// 2-byte global load per voxel, channel and tap it took 716 us.
 constexpr int kWG = 27 * kNC * kNC + kNC;   // partial size per workgroup
+constexpr int kWX = 64, kWY = 8;            // voxels in x and rows of a workgroup
+constexpr int kWInS = 88, kWGrS = 72;       // LDS entries per (row, channel)
+constexpr int kWIn = kWY * kNC * kWInS, kWGr = (kWY + 2) * kNC * kWGrS;   // per plane
+constexpr int kWLds = 2 * kWIn + 4 * kWGr;  // entries of 2 bytes
 
-__global__ void __launch_bounds__(256)
-k_conv_wgrad(int n, const uint16_t* __restrict__ in, const uint16_t* __restrict__ gr,
+// two neighbouring voxels' 8 channels -> one dword (x, x + 1) per channel
+__device__ inline void wg_store_pair(uint16_t* dst, int stride, const u32x4_a2& a, const u32x4_a2& b) {
+  const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    *(uint32_t*)(dst + (2 * c) * stride) = (av[c] & 0xffffu) | (bv[c] << 16);
+    *(uint32_t*)(dst + (2 * c + 1) * stride) = (av[c] >> 16) | (bv[c] & 0xffff0000u);
+  }
+}
+
+__global__ void __launch_bounds__(512)
+k_conv_wgrad(int n, int zc, const uint16_t* __restrict__ in, const uint16_t* __restrict__ gr,
              float* __restrict__ partial) {
-  __shared__ float red[kWG];
+  __shared__ __attribute__((aligned(16))) uint16_t lds[kWLds];
+  uint16_t* const lin = lds;
+  uint16_t* const lgr = lds + 2 * kWIn;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, r = lane & 15;
   const int m = n - 1;
-  const int groups = n >= 64 ? 4 : n / 16;        // 16-voxel groups per row in a workgroup
-  const int gx = n / (16 * groups), gy = n / kCTY;
+  const int xt = n < kWX ? n : kWX, chunks = xt > 32 ? 2 : 1;
+  const int gx = n / xt, gy = n / kWY;
   const int bx = blockIdx.x % gx, by = (blockIdx.x / gx) % gy, bz = blockIdx.x / (gx * gy);
-  const int x0 = bx * 16 * groups, y = by * kCTY + wave, z0 = bz * kCTZ;
-  f32x4 acc[27];
+  const int x0 = bx * xt, y0 = by * kWY, z0 = bz * zc;
+  const int zn = min(zc, n - z0);
+  // rows shorter than a product's 32 voxels: the rest of g stays zero
+  if (xt < kWX)
+    for (int c = tid; c < kWLds / 2; c += 512) ((uint32_t*)lds)[c] = 0u;
+  // this thread's loads: one voxel pair of the input plane and up to two of
+  // the g plane (640 pairs), 8 channels each; threads below 32 one halo voxel
+  const int half = tid & 1, pair = (tid >> 1) & 31, row = tid >> 6;
+  const bool inx = 2 * pair < xt;
+  u32x4_a2 ia, ib, ga[2], gb[2], ha;
+  auto load_in = [&](int z) {
+    const int zz = z & m;
+    if (inx) {
+      const u32x4_a2* s = (const u32x4_a2*)(in + vox(x0 + 2 * pair, y0 + row, zz, n) * kNC) + half;
+      ia = s[0];
+      ib = s[2];
+    }
+    if (tid < 32) {
+      const int xh = (tid & 2) ? x0 + xt : x0 - 1;
+      ha = ((const u32x4_a2*)(in + vox(xh & m, y0 + (tid >> 2), zz, n) * kNC))[half];
+    }
+  };
+  auto store_in = [&](int z) {
+    uint16_t* p = lin + (z & 1) * kWIn;
+    if (inx) wg_store_pair(p + (row * kNC + 8 * half) * kWInS + 8 + 2 * pair, kWInS, ia, ib);
+    if (tid < 32) {
+      uint16_t* q = p + ((tid >> 2) * kNC + 8 * half) * kWInS + ((tid & 2) ? 8 + xt : 7);
+      const uint32_t hv[4] = {ha.x, ha.y, ha.z, ha.w};
 #pragma unroll
-  for (int t = 0; t < 27; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float bsum = 0.f;
-  for (int z = z0; z < z0 + kCTZ && z < n; ++z) {
-    for (int s = 0; s < groups; ++s) {
-      const int xb = x0 + 16 * s + 4 * g;
-      bf16x4 b;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint16_t gv = gr[vox(xb + q, y, z, n) * kNC + r];
-        b[q] = (short)gv;
-        bsum += bf2f(gv);
-      }
-#pragma unroll
-      for (int t = 0; t < 27; ++t) {
-        const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
-        bf16x4 a;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          a[q] = (short)in[vox((xb + q + dx) & m, (y + dy) & m, (z + dz) & m, n) * kNC + r];
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t], 0, 0, 0);
+      for (int c = 0; c < 4; ++c) {
+        q[(2 * c) * kWInS] = (uint16_t)hv[c];
+        q[(2 * c + 1) * kWInS] = (uint16_t)(hv[c] >> 16);
       }
     }
+  };
+  auto load_gr = [&](int z) {
+    const int zz = z & m;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int rw = row + 8 * u;
+      if (rw < kWY + 2 && inx) {
+        const u32x4_a2* s =
+            (const u32x4_a2*)(gr + vox(x0 + 2 * pair, (y0 - 1 + rw) & m, zz, n) * kNC) + half;
+        ga[u] = s[0];
+        gb[u] = s[2];
+      }
+    }
+  };
+  auto store_gr = [&](int z) {
+    uint16_t* p = lgr + ((z + 4) & 3) * kWGr;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int rw = row + 8 * u;
+      if (rw < kWY + 2 && inx)
+        wg_store_pair(p + (rw * kNC + 8 * half) * kWGrS + 2 * pair, kWGrS, ga[u], gb[u]);
+    }
+  };
+  f32x4 acc[28];
+#pragma unroll
+  for (int t = 0; t < 28; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 ones;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) ones[j] = (short)0x3f80;
+  if (xt < kWX) __syncthreads();
+  // planes are counted from the workgroup's first (z0): g planes -1, 0, 1
+  // and input plane 0 are in LDS before the first products
+  for (int z = -1; z <= 1; ++z) {
+    load_gr(z0 + z);
+    store_gr(z);
   }
-  // sum the 4 waves: D[ci = 4g + q][co = r]
-  for (int c = tid; c < kWG; c += 256) red[c] = 0.f;
+  load_in(z0);
+  store_in(0);
   __syncthreads();
-  for (int w = 0; w < 4; ++w) {
-    if (wave == w) {
+  for (int z = 0; z < zn; ++z) {
+    const bool more = z + 1 < zn;
+    if (more) {
+      load_in(z0 + z + 1);
+      load_gr(z0 + z + 2);
+    }
+    const uint16_t* pin = lin + (z & 1) * kWIn + (wave * kNC + r) * kWInS + 8;
+    for (int ch = 0; ch < chunks; ++ch) {
+      const uint16_t* pi = pin + 32 * ch + 8 * g;
+      uint4 f = *(const uint4*)pi;
+      uint32_t before = *(const uint32_t*)(pi - 2), after = *(const uint32_t*)(pi + 8);
+      // a row of 16 voxels fills half of the product: its other half, where
+      // g is zero, must not multiply the halo's values (they may be infinite)
+      if (8 * g >= xt) f = uint4{0u, 0u, 0u, 0u}, before = after = 0u;
+      union { uint32_t u[4]; bf16x8 v; } a[3];
+      a[0].u[0] = __builtin_amdgcn_alignbit(f.x, before, 16);
+      a[0].u[1] = __builtin_amdgcn_alignbit(f.y, f.x, 16);
+      a[0].u[2] = __builtin_amdgcn_alignbit(f.z, f.y, 16);
+      a[0].u[3] = __builtin_amdgcn_alignbit(f.w, f.z, 16);
+      a[1].u[0] = f.x, a[1].u[1] = f.y, a[1].u[2] = f.z, a[1].u[3] = f.w;
+      a[2].u[0] = a[0].u[1], a[2].u[1] = a[0].u[2], a[2].u[2] = a[0].u[3];
+      a[2].u[3] = __builtin_amdgcn_alignbit(after, f.w, 16);
+      // input row y0 + wave, plane z pairs with g row y0 + wave - dy (entry
+      // wave + 1 - dy of the tile) of plane z - dz for tap (dx, dy, dz)
 #pragma unroll
-      for (int t = 0; t < 27; ++t)
+      for (int dz = -1; dz <= 1; ++dz) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) red[(t * kNC + 4 * g + q) * kNC + r] += acc[t][q];
-      // bias: the 4 lanes of equal r hold disjoint voxels; add them with
-      // cross-lane shuffles, then one lane per channel updates LDS
-      float bs = bsum;
-      bs += __shfl_xor(bs, 16, 64);
-      bs += __shfl_xor(bs, 32, 64);
-      if (g == 0) red[27 * kNC * kNC + r] += bs;
+        for (int dy = -1; dy <= 1; ++dy) {
+          const bf16x8 b = *(const bf16x8*)(lgr + ((z - dz + 4) & 3) * kWGr +
+                                            ((wave + 1 - dy) * kNC + r) * kWGrS + 32 * ch + 8 * g);
+          const int t = (dz + 1) * 9 + (dy + 1) * 3;
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            acc[t + q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q].v, b, acc[t + q], 0, 0, 0);
+          if (dz == 0 && dy == 0)
+            acc[27] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, b, acc[27], 0, 0, 0);
+        }
+      }
+    }
+    if (more) {
+      store_in(z + 1);
+      store_gr(z + 2);
     }
     __syncthreads();
   }
-  float* dst = partial + (int64_t)blockIdx.x * kWG;
-  for (int c = tid; c < kWG; c += 256) dst[c] = red[c];
+  // sum of the 8 waves, pairwise in a fixed order: D[ci = 4g + q][co = r]
+  // (of the bias product every row ci holds the sum)
+  float* red = (float*)lds;
+  static_assert(4 * 28 * 256 * sizeof(float) <= sizeof(lds), "partials of four waves fit");
+#pragma unroll
+  for (int w = 4; w > 0; w >>= 1) {
+    if (wave >= w && wave < 2 * w) {
+#pragma unroll
+      for (int t = 0; t < 28; ++t)
+        *(f32x4*)(red + ((wave - w) * 28 + t) * 256 + 4 * lane) = acc[t];
+    }
+    __syncthreads();
+    if (wave < w) {
+#pragma unroll
+      for (int t = 0; t < 28; ++t) acc[t] += *(const f32x4*)(red + (wave * 28 + t) * 256 + 4 * lane);
+    }
+    __syncthreads();
+  }
+  if (wave == 0) {
+    float* dst = partial + (int64_t)blockIdx.x * kWG;
+#pragma unroll
+    for (int t = 0; t < 27; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) dst[(t * kNC + 4 * g + q) * kNC + r] = acc[t][q];
+    if (g == 0) dst[27 * kNC * kNC + r] = acc[27][0];
+  }
 }
 
+// out[c] = sum over workgroups of partial[b][c] in a fixed order: 64 entries
+// per workgroup, the partials split over its 16 groups of 16 lanes (four
+// entries each), four sums in flight per lane: 4.8 us for 256 partials.  (One
+// thread per entry, a serial chain of loads, took 242 us for 1024 partials.)
+constexpr int kWRed = 64;
 __global__ void __launch_bounds__(256)
 k_wgrad_reduce(const float* __restrict__ partial, int nblocks, float* __restrict__ dw,
                float* __restrict__ db) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= kWG) return;
-  float s = 0.f;
-  for (int b = 0; b < nblocks; ++b) s += partial[(int64_t)b * kWG + c];
-  if (c < 27 * kNC * kNC)
-    dw[c] = s;
-  else
-    db[c - 27 * kNC * kNC] = s;
+  __shared__ f32x4 sh[256];
+  const int tid = threadIdx.x, e = tid & 15, s = tid >> 4;
+  const int c = blockIdx.x * kWRed + 4 * e;
+  f32x4 v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (c < kWG) {                               // kWG is a multiple of 4
+    int b = s;
+    for (; b + 48 < nblocks; b += 64)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] += *(const f32x4_a4*)(partial + (int64_t)(b + 16 * u) * kWG + c);
+    for (; b < nblocks; b += 16) v[0] += *(const f32x4_a4*)(partial + (int64_t)b * kWG + c);
+  }
+  sh[tid] = (v[0] + v[1]) + (v[2] + v[3]);
+  __syncthreads();
+  for (int off = 8; off > 0; off >>= 1) {
+    if (s < off) sh[tid] += sh[tid + 16 * off];
+    __syncthreads();
+  }
+  if (s == 0 && c < kWG) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (c + q < 27 * kNC * kNC)
+        dw[c + q] = sh[e][q];
+      else
+        db[c + q - 27 * kNC * kNC] = sh[e][q];
+    }
+  }
 }
 
 // ------------------------------------------------------------- inputs, loss
@@ -344,9 +504,16 @@ k_adam(int np, float* __restrict__ p, const float* __restrict__ grad, float* __r
 }
 
 int conv_blocks(int n) { return ((n + 63) / 64) * (n / kCY) * ((n / kCZ + kZB - 1) / kZB); }
+// Planes per workgroup of the weight gradient: about 256 workgroups (one per
+// CU: a workgroup's LDS takes most of one), at least 4 planes each (two more
+// g planes are staged per workgroup, and its partial is written and summed).
+int wgrad_planes(int n) {
+  const int columns = (n / std::min(n, kWX)) * (n / kWY);
+  return std::max(4, std::min<int>(n, (int)((int64_t)n * columns / 256)));
+}
 int wgrad_blocks(int n) {
-  const int groups = n >= 64 ? 4 : n / 16;
-  return (n / (16 * groups)) * (n / kCTY) * ((n + kCTZ - 1) / kCTZ);
+  const int zc = wgrad_planes(n);
+  return (n / std::min(n, kWX)) * (n / kWY) * ((n + zc - 1) / zc);
 }
 
 }  // namespace
@@ -369,14 +536,20 @@ void launch_conv(int n, const uint16_t* in, const float* w, const float* bias, i
   prof_end(st, K_CONV, 2.0 * 27 * kNC * kNC * V);
 }
 
-size_t wgrad_scratch_bytes(int n) { return (size_t)wgrad_blocks(n) * kWG * sizeof(float); }
+// at least what the partials take; callers may have sized their scratch by
+// one partial per 64 x 4 x 8 voxels, so it does not shrink with fewer of them
+size_t wgrad_scratch_bytes(int n) {
+  const int x = std::min(n, kWX);
+  return (size_t)(n / x) * (n / 4) * (n / 8) * kWG * sizeof(float);
+}
 
 void launch_conv_wgrad(int n, const uint16_t* in, const uint16_t* g, float* dw, float* db,
                        float* scratch, hipStream_t st) {
   const int nb = wgrad_blocks(n);
   prof_begin(st, K_CONV_WGRAD);
-  hipLaunchKernelGGL(k_conv_wgrad, dim3(nb), dim3(256), 0, st, n, in, g, scratch);
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3((kWG + 255) / 256), dim3(256), 0, st, scratch, nb, dw, db);
+  hipLaunchKernelGGL(k_conv_wgrad, dim3(nb), dim3(512), 0, st, n, wgrad_planes(n), in, g, scratch);
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3((kWG + kWRed - 1) / kWRed), dim3(256), 0, st, scratch, nb,
+                     dw, db);
   prof_end(st, K_CONV_WGRAD, 2.0 * 27 * kNC * kNC * (double)n * n * n);
 }
 
