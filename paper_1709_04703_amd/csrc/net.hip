@@ -28,6 +28,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // 16 bytes from memory of the callers' own alignment (2 bytes for BF16
 // activations, 4 for FP32 scratch)
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kNC = 16;                 // channels
@@ -51,30 +52,66 @@ __device__ inline int64_t vox(int i, int j, int k, int n) { return ((int64_t)k *
 // lane / 16, r = lane % 16): A[r][8g .. 8g+7], B[8g .. 8g+7][r],
 // D[4g .. 4g+3][r].  Taps are paired along x: one MFMA takes dx = -1 (k < 16)
 // and dx = 0 (k >= 16) of an input row, a second dx = +1 (k < 16; the other
-// half has zero weights).  A workgroup walks kZB blocks of kCZ planes; for
-// each it holds the input voxels (64 + 2) x (kCY + 2) x (kCZ + 2) in an LDS
-// ring of kBZ planes (consecutive blocks share two planes, so a block loads
-// kCZ new ones); each of its 4 waves owns 16 output voxels in x for all
-// kCY x kCZ output rows and reuses every input-row fragment it loads for the
-// (up to 9) output rows that row feeds.  The weights stay in registers for
-// all blocks.
+// half has zero weights).
+//
+// A workgroup takes a column of 64 voxels in x (its 4 waves 16 each) and kCY
+// rows and marches the input planes of its zc output planes.  Only one input
+// plane is needed at a time: a wave reads each of its kCY + 2 rows once and
+// adds it to the up to nine output rows it feeds, in three planes of
+// accumulators (the plane that starts with this input plane, the one in its
+// middle, the one it completes), whose roles rotate (the loop is unrolled by
+// three so that they stay in registers).  Two LDS slots take the planes in
+// turn; the next plane's global loads are in flight during a plane's
+// products, and one barrier per plane separates writes from reads.  The
+// weights stay in registers.  A tap's contributions are added plane by plane
+// and row by row, as in a block of planes held at once, so results do not
+// depend on zc.
+// Bound by HBM and L2 (64 bytes per voxel and the halos; 96 with the mask)
+// once two workgroups share a CU: 128^3 takes 57 us forward and 69 us backward
+// with the mask, 256^3 346 and 428 us (blocks of 4 planes loaded between
+// barriers, one workgroup per CU at 128^3: 96, 120, 552 and 705 us).
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
-constexpr int kCY = 4, kCZ = 4;                  // output rows per block (y, z)
-constexpr int kZB = 8;                           // z blocks per workgroup (weights loaded once)
-constexpr int kBX = 64 + 2, kBY = kCY + 2, kBZ = kCZ + 2;
+constexpr int kBX = 64 + 2;
 
-template <int FLAGS>
-__global__ void __launch_bounds__(256)
-k_conv(int n, const uint16_t* __restrict__ in, const float* __restrict__ w,
+template <int FLAGS, int kCY>
+__global__ void __launch_bounds__(256, 2)
+k_conv(int n, int zc, const uint16_t* __restrict__ in, const float* __restrict__ w,
        const float* __restrict__ bias, const uint16_t* __restrict__ mask, void* __restrict__ out) {
   constexpr bool RELU = FLAGS & 1, OUT0 = FLAGS & 2, BWD = FLAGS & 4, MASK = FLAGS & 8;
-  __shared__ __attribute__((aligned(16))) uint16_t blk[kBZ][kBY][kBX][kNC];
+  constexpr int kBY = kCY + 2;
+  constexpr int kBUnits = kBY * kBX * 2;           // 16-byte units of an input plane's tile
+  constexpr int kBLoads = (kBUnits + 255) / 256;   // per thread
+  __shared__ u32x4 blk[2][kBUnits];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, r = lane & 15, hi = g >> 1, cg = g & 1;
   const int m = n - 1;
   const int gx = (n + 63) / 64, gy = n / kCY;
-  const int bx = blockIdx.x % gx, by = (blockIdx.x / gx) % gy, bz = blockIdx.x / (gx * gy);
-  const int x0 = bx * 64, y0 = by * kCY;
+  const int b = (int)xcd_block();
+  const int bx = b % gx, by = (b / gx) % gy, bz = b / (gx * gy);
+  const int x0 = bx * 64, y0 = by * kCY, z0 = bz * zc;
+  const int zn = min(zc, n - z0);                // output planes z0 .. z0 + zn - 1
+  // this thread's units of a plane's tile (rows y0 - 1 .. y0 + kCY, voxels
+  // x0 - 1 .. x0 + 64, two units per voxel): offsets within a plane
+  int off[kBLoads];
+#pragma unroll
+  for (int u = 0; u < kBLoads; ++u) {
+    const int c = tid + 256 * u, v = c >> 1;
+    const int px = v % kBX, py = v / kBX;
+    off[u] = (((y0 - 1 + py) & m) * n + ((x0 - 1 + px) & m)) * 2 + (c & 1);
+  }
+  u32x4 nxt[kBLoads];
+  auto load = [&](int z) {
+    const u32x4* p = (const u32x4*)(in + (int64_t)(z & m) * n * n * kNC);
+#pragma unroll
+    for (int u = 0; u < kBLoads; ++u)
+      if (tid + 256 * u < kBUnits) nxt[u] = p[off[u]];
+  };
+  auto store = [&](int slot) {
+#pragma unroll
+    for (int u = 0; u < kBLoads; ++u)
+      if (tid + 256 * u < kBUnits) blk[slot][tid + 256 * u] = nxt[u];
+  };
+  load(z0 - 1);
   // weight fragments per (dy, dz): a01 = taps dx = -1 (k < 16), dx = 0 (k >= 16);
   // a2 = tap dx = +1 (k < 16), zero for k >= 16.  Element j of lane (g, r):
   // input channel 8 cg + j, output channel r.
@@ -96,81 +133,83 @@ k_conv(int n, const uint16_t* __restrict__ in, const float* __restrict__ w,
 #pragma unroll
     for (int q = 0; q < 4; ++q) bq[q] = bias[4 * g + q];
   }
-  for (int zb = 0; zb < kZB; ++zb) {
-  const int z0 = (bz * kZB + zb) * kCZ;
-  if (z0 >= n) break;
-  __syncthreads();                               // the planes to overwrite are consumed
-  // input plane z0 - 1 + pz sits in ring slot (kCZ zb + pz) % kBZ; planes
-  // pz < 2 were loaded with the previous block.  16 bytes per load.
-  const int pz0 = zb == 0 ? 0 : 2;
-  for (int c = tid; c < (kBZ - pz0) * kBY * kBX * 2; c += 256) {
-    const int half = c & 1, v = c >> 1;
-    const int px = v % kBX, py = (v / kBX) % kBY, pz = pz0 + v / (kBX * kBY);
-    const int xx = (x0 - 1 + px) & m, yy = (y0 - 1 + py) & m, zz = (z0 - 1 + pz) & m;
-    ((uint4*)&blk[(kCZ * zb + pz) % kBZ][py][px][0])[half] =
-        ((const uint4*)(in + vox(xx, yy, zz, n) * kNC))[half];
-  }
-  f32x4 acc[kCZ][kCY];
-#pragma unroll
-  for (int a = 0; a < kCZ; ++a)
-#pragma unroll
-    for (int b = 0; b < kCY; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  store(0);
   __syncthreads();
-  // output voxel x0 + 16 wave + r reads block column 16 wave + r + 1 + dx
+  f32x4 acc[3][kCY];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int y = 0; y < kCY; ++y) acc[a][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // output voxel x0 + 16 wave + r reads tile column 16 wave + r + 1 + dx
   const int col = 16 * wave + r + 1;
+  const int x = (x0 + 16 * wave + r) & m;
+  // step s takes input plane z0 - 1 + s: dz = -1 of output plane s (which it
+  // starts), dz = 0 of s - 1, dz = +1 of s - 2 (which it completes)
+  for (int s0 = 0; s0 < zn + 2; s0 += 3) {
 #pragma unroll
-  for (int pz = 0; pz < kBZ; ++pz) {
+    for (int q3 = 0; q3 < 3; ++q3) {
+      const int s = s0 + q3;
+      if (s >= zn + 2) break;                    // uniform
+      if (s + 1 < zn + 2) load(z0 + s);
+      const bool done = s >= 2;
+      const int zo = z0 + s - 2;
+      bf16x4 mk[MASK ? kCY : 1];
+      if (MASK && done) {
 #pragma unroll
-    for (int py = 0; py < kBY; ++py) {
-      // F01: k < 16 from x - 1, k >= 16 from x; F2: x + 1 (both halves)
-      const int sl = (kCZ * zb + pz) % kBZ;
-      const bf16x8 f01 = *(const bf16x8*)&blk[sl][py][col - 1 + hi][8 * cg];
-      const bf16x8 f2 = *(const bf16x8*)&blk[sl][py][col + 1][8 * cg];
+        for (int y = 0; y < kCY; ++y)
+          mk[y] = *(const bf16x4*)(mask + vox(x, y0 + y, zo, n) * kNC + 4 * g);
+      }
 #pragma unroll
-      for (int dz = -1; dz <= 1; ++dz) {
-        const int oz = pz - 1 - dz;            // output row fed with this tap
-        if (oz < 0 || oz >= kCZ) continue;
+      for (int y = 0; y < kCY; ++y) acc[q3][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const u32x4* tile = blk[s & 1];
 #pragma unroll
-        for (int dy = -1; dy <= 1; ++dy) {
-          const int oy = py - 1 - dy;
-          if (oy < 0 || oy >= kCY) continue;
-          const int yz = (dz + 1) * 3 + (dy + 1);
-          acc[oz][oy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a01[yz], f01, acc[oz][oy], 0, 0, 0);
-          acc[oz][oy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[yz], f2, acc[oz][oy], 0, 0, 0);
+      for (int py = 0; py < kBY; ++py) {
+        // F01: k < 16 from x - 1, k >= 16 from x; F2: x + 1 (both halves)
+        const bf16x8 f01 = *(const bf16x8*)&tile[(py * kBX + col - 1 + hi) * 2 + cg];
+        const bf16x8 f2 = *(const bf16x8*)&tile[(py * kBX + col + 1) * 2 + cg];
+#pragma unroll
+        for (int dz = -1; dz <= 1; ++dz) {
+          f32x4* ac = acc[(q3 + 3 - (dz + 1)) % 3];
+#pragma unroll
+          for (int dy = -1; dy <= 1; ++dy) {
+            const int oy = py - 1 - dy;
+            if (oy < 0 || oy >= kCY) continue;
+            const int yz = (dz + 1) * 3 + (dy + 1);
+            ac[oy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a01[yz], f01, ac[oy], 0, 0, 0);
+            ac[oy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[yz], f2, ac[oy], 0, 0, 0);
+          }
         }
       }
+      if (done) {
+        // D[co = 4g + q][voxel = r] of each output row
+#pragma unroll
+        for (int y = 0; y < kCY; ++y) {
+          const int64_t v = vox(x, y0 + y, zo, n);
+          float val[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            float a = acc[(q3 + 1) % 3][y][q] + bq[q];
+            if (RELU) a = a > 0.f ? a : 0.f;
+            val[q] = a;
+          }
+          if (MASK) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (!(bf2f((uint16_t)mk[y][q]) > 0.f)) val[q] = 0.f;
+          }
+          if (OUT0) {
+            if (g == 0) ((float*)out)[v] = val[0];
+          } else {
+            bf16x4 o;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = (short)f2bf(val[q]);
+            *(bf16x4*)((uint16_t*)out + v * kNC + 4 * g) = o;
+          }
+        }
+      }
+      if (s + 1 < zn + 2) store((s + 1) & 1);
+      __syncthreads();
     }
-  }
-  // D[co = 4g + q][voxel = r] of each output row
-  const int x = (x0 + 16 * wave + r) & m;
-#pragma unroll
-  for (int oz = 0; oz < kCZ; ++oz) {
-#pragma unroll
-    for (int oy = 0; oy < kCY; ++oy) {
-      const int64_t v = vox(x, (y0 + oy) & m, (z0 + oz) & m, n);
-      float val[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float a = acc[oz][oy][q] + bq[q];
-        if (RELU) a = a > 0.f ? a : 0.f;
-        val[q] = a;
-      }
-      if (MASK) {
-        const bf16x4 mk = *(const bf16x4*)(mask + v * kNC + 4 * g);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (!(bf2f((uint16_t)mk[q]) > 0.f)) val[q] = 0.f;
-      }
-      if (OUT0) {
-        if (g == 0) ((float*)out)[v] = val[0];
-      } else {
-        bf16x4 o;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = (short)f2bf(val[q]);
-        *(bf16x4*)((uint16_t*)out + v * kNC + 4 * g) = o;
-      }
-    }
-  }
   }
 }
 
@@ -503,7 +542,19 @@ k_adam(int np, float* __restrict__ p, const float* __restrict__ grad, float* __r
   p[q] -= lr * (a / c1) / (sqrtf(b / c2) + eps);
 }
 
-int conv_blocks(int n) { return ((n + 63) / 64) * (n / kCY) * ((n / kCZ + kZB - 1) / kZB); }
+// Rows per workgroup of a layer: 8 read fewer halo rows (1.25x against 1.5x);
+// with the mask their accumulators, weights and prefetched values need more
+// than the 256 registers of two waves per SIMD, and 4 rows are faster where
+// the grid fills the card (256^3: 428 against 535 us, 128^3: 69 against 87 us;
+// 64^3: 36 against 30 us; without the mask 256^3: 356 against 346 us).
+int conv_rows(int n, int flags) { return (flags & 8) && n >= 128 ? 4 : 8; }
+// Output planes per workgroup: about 512 workgroups (two per CU, so that one's
+// products cover the other's barriers; 1024 measured 79 against 57 us at
+// 128^3), at least 2 planes each (a workgroup reads two more).
+int conv_planes(int n, int rows) {
+  const int columns = ((n + 63) / 64) * (n / rows);
+  return std::max(2, std::min<int>(n, (int)((int64_t)n * columns / 512)));
+}
 // Planes per workgroup of the weight gradient: about 256 workgroups (one per
 // CU: a workgroup's LDS takes most of one), at least 4 planes each (two more
 // g planes are staged per workgroup, and its partial is written and summed).
@@ -522,15 +573,21 @@ bool net_size_ok(int n) { return n >= 16 && (n & (n - 1)) == 0; }
 
 void launch_conv(int n, const uint16_t* in, const float* w, const float* bias, int flags,
                  const uint16_t* mask, void* out, hipStream_t st) {
-  const dim3 g(conv_blocks(n));
+  const int rows = conv_rows(n, flags), zc = conv_planes(n, rows);
+  const dim3 g(((n + 63) / 64) * (n / rows) * ((n + zc - 1) / zc));
   const double V = (double)n * n * n;
   prof_begin(st, K_CONV);
   switch (flags) {
-    case 1: hipLaunchKernelGGL(k_conv<1>, g, dim3(256), 0, st, n, in, w, bias, mask, out); break;
-    case 2: hipLaunchKernelGGL(k_conv<2>, g, dim3(256), 0, st, n, in, w, bias, mask, out); break;
-    case 4: hipLaunchKernelGGL(k_conv<4>, g, dim3(256), 0, st, n, in, w, bias, mask, out); break;
-    case 12: hipLaunchKernelGGL(k_conv<12>, g, dim3(256), 0, st, n, in, w, bias, mask, out); break;
-    default: hipLaunchKernelGGL(k_conv<0>, g, dim3(256), 0, st, n, in, w, bias, mask, out); break;
+    case 1: hipLaunchKernelGGL((k_conv<1, 8>), g, dim3(256), 0, st, n, zc, in, w, bias, mask, out); break;
+    case 2: hipLaunchKernelGGL((k_conv<2, 8>), g, dim3(256), 0, st, n, zc, in, w, bias, mask, out); break;
+    case 4: hipLaunchKernelGGL((k_conv<4, 8>), g, dim3(256), 0, st, n, zc, in, w, bias, mask, out); break;
+    case 12:
+      if (rows == 4)
+        hipLaunchKernelGGL((k_conv<12, 4>), g, dim3(256), 0, st, n, zc, in, w, bias, mask, out);
+      else
+        hipLaunchKernelGGL((k_conv<12, 8>), g, dim3(256), 0, st, n, zc, in, w, bias, mask, out);
+      break;
+    default: hipLaunchKernelGGL((k_conv<0, 8>), g, dim3(256), 0, st, n, zc, in, w, bias, mask, out); break;
   }
   // matrix-core work: 27 taps x 16 x 16 MACs per voxel
   prof_end(st, K_CONV, 2.0 * 27 * kNC * kNC * V);
