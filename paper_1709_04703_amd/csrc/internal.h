@@ -180,9 +180,10 @@ size_t pk_workspace_bytes(int n);
 int power_spectrum(const double* const x[3], int64_t npart, double box, int n, int flags,
                    void* ws, hipStream_t st, double* k_out, double* p_out, double* praw_out,
                    int64_t* modes_out, char* msg, size_t len);
-// One ADE sweep of phi over box b with source f (ade.hip).
+// One ADE sweep of phi over box b with source f (ade.hip); scratch: 4 n^3
+// bytes (rows passed between workgroups).
 void launch_ade_sweep(double* phi, const double* f, int n, const Box& b, bool periodic, double lam,
-                      bool forward, hipStream_t st);
+                      bool forward, void* scratch, hipStream_t st);
 // One V-cycle for A_0 e = r_0; returns the level-0 buffer holding e.  With
 // fine_start the cycle improves the e already on level 0 (a further cycle on
 // the same r_0), else it starts from e = 0.  Levels with the fused sweeps

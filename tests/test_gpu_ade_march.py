@@ -1,0 +1,80 @@
+"""The ADE sweep where its split over workgroups and lanes changes: the
+smallest mesh, planes that do not fill the last workgroup, rows of one to eight
+cells per lane with a ragged end, and sweeps that follow each other on the same
+scratch.  Each cell's own update equation fixes the result: earlier neighbours
+new, later ones old."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from oracle import ade
+
+from helpers import lib_config, make_sim
+
+pytestmark = pytest.mark.gpu
+
+
+def _box_residual(old, new, f, lam, lo, hi, forward):
+    """Largest |(1 + 3 lam) new - (1 - 3 lam) old - lam (S6 - f)| over the box;
+    outside it old and new are the same frozen values."""
+    sl = [slice(lo[d], hi[d] + 1) for d in (2, 1, 0)]
+    s = 0.0
+    for ax in range(3):
+        for step in (-1, 1):
+            nb = list(sl)
+            nb[ax] = slice(sl[ax].start + step, sl[ax].stop + step)
+            s = s + ((new if (step < 0) == forward else old)[tuple(nb)])
+    c = tuple(sl)
+    return np.abs((1 + 3 * lam) * new[c] - (1 - 3 * lam) * old[c] - lam * (s - f[c])).max()
+
+
+@pytest.mark.parametrize("forward", [True, False])
+def test_smallest_periodic_mesh(forward):
+    ng, lam = 8, 8.8
+    rng = np.random.default_rng(1)
+    old, f = rng.normal(size=(ng,) * 3), rng.normal(size=(ng,) * 3)
+    cfg = lib_config(ng, 100.0, c_grav=-1.0, precision=0, n_initial=1, solver=1)
+    sim = make_sim(cfg, 1)
+    sim.bind([[50.0, 50.0, 50.0]], [[0.0, 0.0, 0.0]], [0], phi=old)
+    import torch
+
+    sim.rhs.copy_(torch.as_tensor(f))
+    sim.ade_sweep(lam, forward)
+    sim.ade_sweep(lam, not forward)          # again on the scratch of the first
+    ref = ade.sweep(old, f, lam, (0,) * 3, (ng - 1,) * 3, True, forward)
+    ref = ade.sweep(ref, f, lam, (0,) * 3, (ng - 1,) * 3, True, not forward)
+    assert np.abs(sim.phi_numpy() - ref).max() <= 1e-12 * np.abs(ref).max()
+    sim.close()
+
+
+# cells of the box per axis: below, at and above the workgroup's 6 planes; two,
+# four and eight cells per lane
+@pytest.mark.parametrize("ng,cells", [(32, 5), (32, 7), (64, 13), (128, 71), (256, 135), (512, 263)])
+@pytest.mark.parametrize("forward", [True, False])
+def test_ragged_boxes(ng, cells, forward):
+    import torch
+
+    box, lam = 10.0 * ng, 8.8
+    h = box / ng
+    cfg = lib_config(ng, box, c_grav=-1.0, shrink=1, precision=0, n_initial=1, solver=1, box_align=1)
+    sim = make_sim(cfg, 1)
+    gen = torch.Generator(device="cuda:0").manual_seed(ng)
+    old = torch.randn((ng,) * 3, generator=gen, dtype=torch.float64, device="cuda:0")
+    f = torch.randn((ng,) * 3, generator=gen, dtype=torch.float64, device="cuda:0")
+    sim.bind([[0.5 * box] * 3], [[0.0] * 3], [0])
+    sim.shrink_radius((cells - 5) // 2 * h)
+    st = sim.state()
+    lo, hi = st["lo"], st["hi"]
+    assert st["periodic"] == 0 and all(b - a + 1 == cells for a, b in zip(lo, hi))
+    sim.phi.copy_(old)
+    sim.rhs.copy_(f)
+    sim.ade_sweep(lam, forward)
+    new, old, f = sim.phi_numpy(), old.cpu().numpy(), f.cpu().numpy()
+    inside = np.zeros(old.shape, dtype=bool)
+    inside[lo[2]:hi[2] + 1, lo[1]:hi[1] + 1, lo[0]:hi[0] + 1] = True
+    assert np.array_equal(new[~inside], old[~inside])
+    scale = (1.0 + 3.0 * lam) * np.abs(new).max()
+    # the bound of the periodic sweep's own test: 64 roundings of the terms
+    assert _box_residual(old, new, f, lam, lo, hi, forward) <= 1e-14 * 64 * scale
+    sim.close()
