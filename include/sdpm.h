@@ -89,8 +89,8 @@ enum { SDPM_WS_EXTRAP = 4 };
 /* SDPM_SOLVER_FFT: the implicit step (and the initial static solve) solved
  * exactly by FFT while the mesh is periodic (the standard particle-mesh
  * solver the paper compares against, Sec. 2.4, with the 7-point symbol),
- * multigrid once the domain has a frozen exterior; FP64 hipFFT transforms
- * with their work area in the workspace; needs warm_start == SDPM_WS_PREV;
+ * multigrid once the domain has a frozen exterior; FP64 transforms with
+ * their buffers in the workspace; needs warm_start == SDPM_WS_PREV;
  * reports 0 iterations and residual 0 for FFT solves.                      */
 enum { SDPM_SOLVER_IMPLICIT = 0, SDPM_SOLVER_ADE = 1, SDPM_SOLVER_FFT = 2 };
 /* sdpm_config.assignment.  CIC: the 2^3 cells around a particle, axis
@@ -414,8 +414,7 @@ int sdpm_interp_force(sdpm_ctx* ctx, double* g_dev[3]);
  * times (central differences of neighbouring shells, one-sided at the ends,
  * clamped to [-4, 4], 0 where a neighbour is not positive).
  * workspace: device memory of sdpm_pk_workspace_bytes(ng); runs on
- * hip_stream and returns when the results are on the host (the FFT plan is
- * made per call).  Errors: SDPM_EINVAL (arguments), SDPM_ENOMEM (workspace
+ * hip_stream and returns when the results are on the host.  Errors: SDPM_EINVAL (arguments), SDPM_ENOMEM (workspace
  * too small), SDPM_EDOMAIN (a position outside [0, box]), SDPM_EHIP.     */
 enum { SDPM_PK_SHOT = 1, SDPM_PK_JING = 2 };
 int sdpm_pk_workspace_bytes(int32_t ng, int64_t* bytes);

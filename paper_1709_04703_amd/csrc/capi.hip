@@ -37,8 +37,6 @@ struct sdpm_ctx {
   int64_t blk_n = -1;
   float* gmesh = nullptr;       // FP32 force mesh (mixed precision)
   FftPlan fft;                  // periodic FFT solver (SDPM_SOLVER_FFT)
-  void* fft_work = nullptr;
-  size_t fft_work_bytes = 0;
   // learned warm start
   float* net_params = nullptr;
   uint16_t* net_act0 = nullptr;
@@ -244,17 +242,12 @@ size_t carve(const sdpm_config& c, int64_t capacity, char* base, sdpm_ctx* ctx) 
   float* g3 = c.precision == SDPM_MIXED ? (float*)take((size_t)c.ng * c.ng * c.ng * 3 * sizeof(float))
                                         : nullptr;
   if (c.solver == SDPM_SOLVER_FFT) {
-    // half spectrum, the transforms' work area (at most the spectrum's size)
-    // and the symbol table
-    const size_t cb = fft_complex_bytes(c.ng);
-    void* cbuf = take(cb);
-    void* work = take(cb);
+    // the padded half spectrum and the root table, the symbol table
+    void* buf = take(2 * fft_complex_bytes(c.ng));
     double* sym = (double*)take((size_t)c.ng * sizeof(double));
     if (ctx) {
-      ctx->fft.c = cbuf;
+      ctx->fft.c = buf;
       ctx->fft.sym = sym;
-      ctx->fft_work = work;
-      ctx->fft_work_bytes = cb;
     }
   }
   if (c.warm_start & SDPM_WS_EXTRAP) {
@@ -850,7 +843,7 @@ int solve(sdpm_ctx* c, double kappa, int slot, SolveOut* so, RhsOut rh = RhsOut{
     // exact: no iterations, residual at rounding level (reported as 0)
     *so = SolveOut{};
     const int rc = fft_solve(c->fft, c->fields.rhs, c->fields.phi, kappa, c->st);
-    return rc ? fail(c, rc, "hipFFT execution failed") : SDPM_OK;
+    return rc ? fail(c, rc, "launch of the FFT solve failed") : SDPM_OK;
   }
   return c->cfg.precision == SDPM_MIXED ? solve_impl<float>(c, kappa, slot, so, rh)
                                         : solve_impl<double>(c, kappa, slot, so, rh);
@@ -1135,15 +1128,12 @@ int sdpm_create(const sdpm_config* cfg, void* workspace, int64_t ws_bytes, void*
   }
   clear_all_levels(c);
   if (cfg->solver == SDPM_SOLVER_FFT) {
-    char msg[256];
-    const int frc = fft_init(&c->fft, cfg->ng, c->fft.c, c->fft_work, c->fft_work_bytes, c->fft.sym,
-                             c->st, msg, sizeof msg);
-    if (frc) {
-      fft_destroy(&c->fft);
+    fft_init(&c->fft, cfg->ng, c->fft.c, c->fft.sym, c->st);
+    if (hipGetLastError() != hipSuccess) {
       for (auto& e : c->ev) (void)hipEventDestroy(e);
       (void)hipHostFree(c->hpin);
       delete c;
-      return fail(nullptr, frc, "%s", msg);
+      return fail(nullptr, SDPM_EHIP, "launch of the FFT tables failed");
     }
   }
   *out = c;
@@ -1778,7 +1768,6 @@ int sdpm_destroy(sdpm_ctx* c) {
   if (c->st) (void)hipStreamSynchronize(c->st);
   else (void)hipDeviceSynchronize();
   c->prof.release();
-  fft_destroy(&c->fft);
   for (auto& e : c->ev)
     if (e) (void)hipEventDestroy(e);
   (void)hipHostFree(c->hpin);

@@ -160,20 +160,22 @@ void launch_sum_phi(const double* phi, int n, const Box& b, double* partial, int
 void launch_add_const(double* phi, float* chg, int n, const Box& b, double v, hipStream_t st);
 void launch_reduce_final(const double* partial, int nblocks, int nslots, double* out,
                          hipStream_t st);
-// Exact periodic FFT solve of (Lap_h - kappa h^2) phi = rhs (fft.hip): FP64
-// real-to-complex / complex-to-real plans on an n^3 mesh, half-spectrum
-// buffer c, the 1-D symbol table sym (n values) on the device.
+// Exact periodic FFT solve of (Lap_h - kappa h^2) phi = rhs (fft.hip) on an
+// n^3 mesh: the half spectrum c (rows of `pitch` complex values, the first n
+// / 2 + 1 used) and the root table tw share a buffer of 2
+// fft_complex_bytes(n), sym is the 1-D symbol table (n values).
 struct FftPlan {
   int n = 0;
-  void* fwd = nullptr;
-  void* inv = nullptr;
+  int pitch = 0;
   void* c = nullptr;
+  void* tw = nullptr;
   double* sym = nullptr;
 };
 size_t fft_complex_bytes(int n);
-int fft_init(FftPlan* p, int n, void* complex_buf, void* work, size_t work_bytes, double* sym_dev,
-             hipStream_t st, char* msg, size_t len);
-void fft_destroy(FftPlan* p);
+// Sets up p and enqueues the tables' computation.
+void fft_init(FftPlan* p, int n, void* buf, double* sym_dev, hipStream_t st);
+// The half spectrum (unnormalised, e^{-i}) of a real n^3 mesh into p.c.
+void fft_forward(const FftPlan& p, const double* in, hipStream_t st);
 int fft_solve(const FftPlan& p, const double* rhs, double* phi, double kappa_h2, hipStream_t st);
 // Power spectrum of particle positions (pk.hip; see sdpm_power_spectrum).
 size_t pk_workspace_bytes(int n);
