@@ -67,6 +67,15 @@ __host__ __device__ inline int64_t lin(int i, int j, int k, int n) {
   return ((int64_t)k * n + j) * n + i;
 }
 
+// Multigrid arrays (e, r, t of every level) are stored split by colour:
+// the n^3/2 red cells ((i+j+k) even) first, then the black ones, each in
+// row order with x index i >> 1.  A colour sweep then streams contiguous,
+// fully used cache lines.
+__host__ __device__ inline int64_t half_cells(int n) { return (int64_t)n * n * (n >> 1); }
+__host__ __device__ inline int64_t sidx(int i, int j, int k, int n) {
+  return (int64_t)((i + j + k) & 1) * half_cells(n) + ((int64_t)k * n + j) * (n >> 1) + (i >> 1);
+}
+
 inline int64_t box_cells(const Box& b) {
   return (int64_t)(b.hi[0] - b.lo[0] + 1) * (b.hi[1] - b.lo[1] + 1) * (b.hi[2] - b.lo[2] + 1);
 }
@@ -193,6 +202,19 @@ void launch_ade_sweep(double* phi, const double* f, int n, const Box& b, bool pe
 template <typename T>
 const T* vcycle(Level* lv, int nlev, double kappa, int pre, int post, int coarse_sweeps,
                 bool periodic, bool fine_start, hipStream_t st);
+// The passes of a V(2,2) cycle on a smaller level l (tile.hip): down to C's
+// right-hand side (zero: from e = 0, else from L.e), up from C's correction
+// into L.e, and the sweeps of a coarsest level from zero into L.e.  v4: in the
+// order of the 4-cell forms of the separate kernels.
+template <typename T>
+void launch_tile_down(const Level& L, const Level& C, int l, double kappa, bool periodic, bool zero,
+                      bool v4, hipStream_t st);
+template <typename T>
+void launch_tile_up(const Level& L, const Level& C, int l, double kappa, bool periodic, bool v4,
+                    hipStream_t st);
+template <typename T>
+void launch_tile_sweeps(const Level& L, int l, double kappa, bool periodic, int sweeps,
+                        hipStream_t st);
 // Whether a level of n cells a side takes the fused four-sweep kernel (FP32
 // only; smaller levels run too few workgroups for it).
 constexpr int kSweep4Min = 256;

@@ -40,15 +40,6 @@ __device__ inline double block_sum(double v, double* sh) {
   return r;
 }
 
-// Multigrid arrays (e, r, t of every level) are stored split by colour:
-// the n^3/2 red cells ((i+j+k) even) first, then the black ones, each in
-// row order with x index i >> 1.  A colour sweep then streams contiguous,
-// fully used cache lines.
-__host__ __device__ inline int64_t half_cells(int n) { return (int64_t)n * n * (n >> 1); }
-__host__ __device__ inline int64_t sidx(int i, int j, int k, int n) {
-  return (int64_t)((i + j + k) & 1) * half_cells(n) + ((int64_t)k * n + j) * (n >> 1) + (i >> 1);
-}
-
 // Aligned vectors of 2 and 4 values (one wide load or store).
 template <typename T>
 struct alignas(2 * sizeof(T)) Vec2 {
@@ -1458,79 +1449,90 @@ k_prolong_black_v4(const float* __restrict__ ec, float* __restrict__ ef, int nc,
 }
 
 // Coarsest level: one workgroup; e lives in LDS on a box-local array of at
-// most kCoarseMax^3 entries: the whole (periodic) level, or the box plus a
-// one-cell ring of zeros (Dirichlet).  Each thread owns up to kCoarseMax^3 /
-// 1024 cells whose LDS offsets and right-hand sides stay in registers for all
-// `sweeps` red-black sweeps.  With project != 0 (periodic, kappa = 0) the
-// mean of r is removed first and the mean of e afterwards.  The host checks
-// that the local array fits.
-constexpr int kCoarsePer = kCoarseMax * kCoarseMax * kCoarseMax / 1024;
+// most kCoarseMax^3 entries, split by colour: the whole (periodic) level, or
+// the box plus a one-cell ring of zeros (Dirichlet).  Each thread owns up to
+// kCoarsePer cells of either colour, whose LDS offsets, neighbours' offsets
+// and right-hand sides stay in registers for all `sweeps` red-black sweeps, so
+// that every lane works in every half sweep and consecutive lanes read
+// consecutive entries (cells owned regardless of colour, half of the lanes
+// idle: 79 us in FP32, 89 us in FP64 for 64 sweeps of 16^3, now @COARSE@).
+// With project != 0 (periodic, kappa = 0) the mean of r is removed first and
+// the mean of e afterwards.  The host checks that the local array fits.
+constexpr int kCoarsePer = kCoarseMax * kCoarseMax * kCoarseMax / 2048;
+// both colours of an array with odd rows (lx <= 1023) round a row up
+constexpr int kCoarseLds = kCoarseMax * kCoarseMax * kCoarseMax * 3 / 2;
 
 template <typename T>
 __global__ void __launch_bounds__(1024)
 k_coarse(T* __restrict__ e, const T* __restrict__ r, int n, Box b, T scale, T inv_diag,
          int sweeps, int project, int periodic) {
-  __shared__ T es[kCoarseMax * kCoarseMax * kCoarseMax];
-  __shared__ double sh[16];
+  __shared__ T es[kCoarseLds];
+  __shared__ double sh[18];
   const int tid = threadIdx.x;
   const int nx = b.hi[0] - b.lo[0] + 1, ny = b.hi[1] - b.lo[1] + 1, nz = b.hi[2] - b.lo[2] + 1;
-  const int nbox = nx * ny * nz;
   const int off = periodic ? 0 : 1;
   const int lx = nx + 2 * off, ly = ny + 2 * off, lz = nz + 2 * off;
+  const int hl = (lx + 1) >> 1, half = hl * ly * lz;       // entries of a row, of a colour
   const int m = n - 1;
-  for (int c = tid; c < lx * ly * lz; c += 1024) es[c] = 0;
-  // owned cells: local offset of the cell and of its 6 neighbours, colour, rhs
-  int own[kCoarsePer], nbr[kCoarsePer][6], col[kCoarsePer];
-  T rr[kCoarsePer];
-  int64_t gidx[kCoarsePer];
-  int nown = 0;
+  // colours by the mesh's parity: the local array's (0, 0, 0) has parity p0
+  const int p0 = (b.lo[0] + b.lo[1] + b.lo[2] + 3 * off) & 1;
+  auto at = [&](int x, int y, int z) {
+    return (((x + y + z) ^ p0) & 1) * half + (z * ly + y) * hl + (x >> 1);
+  };
+  for (int c = tid; c < 2 * half; c += 1024) es[c] = 0;
+  int own[2][kCoarsePer], nbr[2][kCoarsePer][6];
+  T rr[2][kCoarsePer];
+  int64_t gidx[2][kCoarsePer];
+  bool has[2][kCoarsePer];
   double racc = 0.0;
+  const int hx = (nx + 1) >> 1;
 #pragma unroll
-  for (int u = 0; u < kCoarsePer; ++u) {
-    const int q = tid + 1024 * u;
-    if (q >= nbox) break;
-    nown = u + 1;
-    const int qa = q % nx, qb = (q / nx) % ny, qc = q / (nx * ny);
-    const int a0 = qa + off, b0 = qb + off, c0 = qc + off;
-    int am, ap, bm, bp, cm, cp;
-    if (periodic) {
-      am = (a0 - 1) & m; ap = (a0 + 1) & m;
-      bm = (b0 - 1) & m; bp = (b0 + 1) & m;
-      cm = (c0 - 1) & m; cp = (c0 + 1) & m;
-    } else {
-      am = a0 - 1; ap = a0 + 1; bm = b0 - 1; bp = b0 + 1; cm = c0 - 1; cp = c0 + 1;
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int u = 0; u < kCoarsePer; ++u) {
+      const int q = tid + 1024 * u;
+      const int y0 = q / hx % ny, z0 = q / (hx * ny);
+      const int y = y0 + off, z = z0 + off;
+      // the row's q-th cell of colour c
+      const int x0 = 2 * (q % hx) + ((c + b.lo[0] + b.lo[1] + y0 + b.lo[2] + z0) & 1);
+      const int x = x0 + off;
+      has[c][u] = q < hx * ny * nz && x0 < nx;
+      rr[c][u] = 0;
+      if (!has[c][u]) continue;
+      int xm = x - 1, xp = x + 1, ym = y - 1, yp = y + 1, zm = z - 1, zp = z + 1;
+      if (periodic) xm &= m, xp &= m, ym &= m, yp &= m, zm &= m, zp &= m;
+      own[c][u] = at(x, y, z);
+      nbr[c][u][0] = at(xm, y, z);
+      nbr[c][u][1] = at(xp, y, z);
+      nbr[c][u][2] = at(x, ym, z);
+      nbr[c][u][3] = at(x, yp, z);
+      nbr[c][u][4] = at(x, y, zm);
+      nbr[c][u][5] = at(x, y, zp);
+      gidx[c][u] = sidx(b.lo[0] + x0, b.lo[1] + y0, b.lo[2] + z0, n);
+      rr[c][u] = r[gidx[c][u]];
+      racc += (double)rr[c][u];
     }
-    own[u] = (c0 * ly + b0) * lx + a0;
-    nbr[u][0] = (c0 * ly + b0) * lx + am;
-    nbr[u][1] = (c0 * ly + b0) * lx + ap;
-    nbr[u][2] = (c0 * ly + bm) * lx + a0;
-    nbr[u][3] = (c0 * ly + bp) * lx + a0;
-    nbr[u][4] = (cm * ly + b0) * lx + a0;
-    nbr[u][5] = (cp * ly + b0) * lx + a0;
-    const int i = b.lo[0] + qa, j = b.lo[1] + qb, k = b.lo[2] + qc;
-    col[u] = (i + j + k) & 1;
-    gidx[u] = sidx(i, j, k, n);
-    rr[u] = r[gidx[u]];
-    racc += (double)rr[u];
-  }
+  const int nbox = nx * ny * nz;
   if (project) {
     const double s = block_sum<1024>(racc, sh);
-    if (tid == 0) sh[8] = s / nbox;
+    if (tid == 0) sh[16] = s / nbox;
     __syncthreads();
-    const T rm = (T)sh[8];
+    const T rm = (T)sh[16];
 #pragma unroll
-    for (int u = 0; u < kCoarsePer; ++u)
-      if (u < nown) rr[u] -= rm;
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int u = 0; u < kCoarsePer; ++u) rr[c][u] -= rm;
   }
   __syncthreads();
   for (int sw = 0; sw < sweeps; ++sw) {
-    for (int color = 0; color < 2; ++color) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
 #pragma unroll
       for (int u = 0; u < kCoarsePer; ++u) {
-        if (u >= nown || col[u] != color) continue;
-        const T nb = es[nbr[u][0]] + es[nbr[u][1]] + es[nbr[u][2]] + es[nbr[u][3]] +
-                     es[nbr[u][4]] + es[nbr[u][5]];
-        es[own[u]] = (nb - scale * rr[u]) * inv_diag;
+        if (!has[c][u]) continue;
+        const T nb = es[nbr[c][u][0]] + es[nbr[c][u][1]] + es[nbr[c][u][2]] + es[nbr[c][u][3]] +
+                     es[nbr[c][u][4]] + es[nbr[c][u][5]];
+        es[own[c][u]] = (nb - scale * rr[c][u]) * inv_diag;
       }
       __syncthreads();
     }
@@ -1539,20 +1541,22 @@ k_coarse(T* __restrict__ e, const T* __restrict__ r, int n, Box b, T scale, T in
   if (project) {
     double acc = 0.0;
 #pragma unroll
-    for (int u = 0; u < kCoarsePer; ++u)
-      if (u < nown) acc += (double)es[own[u]];
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int u = 0; u < kCoarsePer; ++u)
+        if (has[c][u]) acc += (double)es[own[c][u]];
     const double s = block_sum<1024>(acc, sh);
-    if (tid == 0) sh[8] = s / nbox;
+    if (tid == 0) sh[17] = s / nbox;
     __syncthreads();
-    emean = (T)sh[8];
+    emean = (T)sh[17];
   }
 #pragma unroll
-  for (int u = 0; u < kCoarsePer; ++u)
-    if (u < nown) e[gidx[u]] = es[own[u]] - emean;
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int u = 0; u < kCoarsePer; ++u)
+      if (has[c][u]) e[gidx[c][u]] = es[own[c][u]] - emean;
 }
 
-// Residual of phi + scale * d, with d applied only inside the box (the
-// learned initial guess); written colour-split like k_residual.
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_residual_guess(const double* __restrict__ phi, const float* __restrict__ d, double scale,
@@ -2382,6 +2386,16 @@ static int sweeps_for_1e3(const Level& L, int l, double kappa, bool periodic) {
   return std::max(1, (int)std::ceil(std::log(1e-3) / (2.0 * std::log(rho))));
 }
 
+// Levels whose way down and way up are one launch each (tile.hip): V(2,2)
+// cycles on meshes of up to 128^3.  The profiler charges their time to the
+// half sweeps in them (all but a red one from zero), with the bytes of as many
+// separate half sweeps.
+constexpr int kTileMax = 64;
+static bool tiles(const Level& L, int pre, int post) { return pre == 2 && post == 2 && L.n <= kTileMax; }
+// whether the separate kernels would take their 4-cell forms on this level
+template <typename T>
+static bool v4_level(const Level& L) { return sizeof(T) == 4 && v4_threads(L.box) != 0; }
+
 template <typename T>
 const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int coarse_sweeps,
                 bool periodic, bool fine_start, hipStream_t st) {
@@ -2411,6 +2425,12 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
     // already there
     const bool zero = !(l == 0 && fine_start);
     const T inv_scale = (T)(1.0 / std::ldexp(1.0, 2 * l));
+    if (tiles(L, pre, post)) {
+      prof_begin(st, l == 0 ? K_SMOOTH : K_SMOOTH_COARSE);
+      launch_tile_down<T>(L, lv[l + 1], l, kappa, periodic, zero, v4_level<T>(L), st);
+      prof_end(st, l == 0 ? K_SMOOTH : K_SMOOTH_COARSE, (zero ? 3 : 4) * 1.5 * es * cells, zero ? 3 : 4);
+      continue;
+    }
     // the fused pre-smoothing forms the red residual itself
     if (!sweeps4<T>(L, l, periodic, pre, zero, scale, inv_diag, st, true, inv_scale, (T)kappa)) {
       sweep_run<T>((T*)L.e, r, L, l, 0, 2 * pre, zero, scale, inv_diag, st);
@@ -2438,6 +2458,10 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
                          L.box, scale, inv_diag, sweeps,
                          (periodic && kappa == 0.0) ? 1 : 0, periodic ? 1 : 0);
       prof_end(st, K_COARSE, 2 * es * (double)box_cells(L.box));
+    } else if (tiles(L, pre, post)) {
+      prof_begin(st, K_SMOOTH_COARSE);
+      launch_tile_sweeps<T>(L, l, kappa, periodic, sweeps, st);
+      prof_end(st, K_SMOOTH_COARSE, 2.0 * sweeps * 1.5 * es * (double)box_cells(L.box), 2 * sweeps);
     } else {
       // a coarsest level beyond the LDS solve (a large degenerate Dirichlet
       // box, or a level the hierarchy ends on early): sweeps through global
@@ -2454,6 +2478,12 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
     const double cells = (double)box_cells(L.box);
     const T scale = (T)std::ldexp(1.0, 2 * l);
     const T inv_diag = (T)(1.0 / (6.0 + std::ldexp(1.0, 2 * l) * kappa));
+    if (tiles(L, pre, post)) {
+      prof_begin(st, l == 0 ? K_SMOOTH : K_SMOOTH_COARSE);
+      launch_tile_up<T>(L, C, l, kappa, periodic, v4_level<T>(L), st);
+      prof_end(st, l == 0 ? K_SMOOTH : K_SMOOTH_COARSE, 4 * 1.5 * es * cells, 4);
+      continue;
+    }
     prof_begin(st, K_PROLONG);
     prolong_level<T>(L, C, post == 0, st);
     prof_end(st, K_PROLONG, es * ((post > 0 ? 1.0 : 2.0) * cells + (double)box_cells(C.box)));
