@@ -1455,11 +1455,11 @@ k_prolong_black_v4(const float* __restrict__ ec, float* __restrict__ ef, int nc,
 // and right-hand sides stay in registers for all `sweeps` red-black sweeps, so
 // that every lane works in every half sweep and consecutive lanes read
 // consecutive entries (cells owned regardless of colour, half of the lanes
-// idle: 79 us in FP32, 89 us in FP64 for 64 sweeps of 16^3, now @COARSE@).
+// idle: 79 us in FP32, 89 us in FP64 for 64 sweeps of 16^3, now 45 and 48).
 // With project != 0 (periodic, kappa = 0) the mean of r is removed first and
 // the mean of e afterwards.  The host checks that the local array fits.
 constexpr int kCoarsePer = kCoarseMax * kCoarseMax * kCoarseMax / 2048;
-// both colours of an array with odd rows (lx <= 1023) round a row up
+// each colour rounds an odd row up to (lx + 1) / 2 entries
 constexpr int kCoarseLds = kCoarseMax * kCoarseMax * kCoarseMax * 3 / 2;
 
 template <typename T>
