@@ -490,33 +490,89 @@ k_drift_deposit(ParticleArgs pa, double coef, MeshMap mm, unsigned long long* __
   }
 }
 
-// g = sum over the S^3 assignment nodes of w * (-grad Phi) (central differences).
+// g = sum over the S^3 assignment nodes of w * (-grad Phi) (central
+// differences).  The weights are products of axis weights, so the sum over
+// nodes of w_i (Phi_{i+1} - Phi_{i-1}) along an axis is one over the S + 2
+// potential values around them with the differences d_i = w_{i-1} - w_{i+1}
+// (exact integers): each value of the potential is loaded once, in 8-byte
+// pairs along a row (CIC 32 values in 16 loads instead of 48 loads, TSC 81 in
+// 51 instead of 162), and every row adds to all three components.  The value
+// at the first node is subtracted from each, which keeps the sums' rounding at
+// that of the potential's differences, as in the node by node form.
+// Bound by the gathers: 5 M particles on 256^3, CIC: 148 us (228 node by
+// node); 15.8 M, TSC with kick and drifts: 835 us (1436).
 template <int S>
 __device__ inline void interp_g(const double* __restrict__ phi, const MeshMap& mm,
                                 const Stencil<S>& c, double inv2h, double g[3]) {
   const int n = mm.ng, m = n - 1;
-  const double norm = ldexp(1.0, -3 * mm.frac_bits);
-  g[0] = g[1] = g[2] = 0.0;
-  for (int dz = 0; dz < S; ++dz) {
-    const int k = (c.cell[2] + dz) & m;
-    const int kp = (k + 1) & m, km = (k - 1) & m;
-    for (int dy = 0; dy < S; ++dy) {
-      const int j = (c.cell[1] + dy) & m;
-      const int jp = (j + 1) & m, jm = (j - 1) & m;
-      const uint64_t wyz = c.w[1][dy] * c.w[2][dz];
-      for (int dx = 0; dx < S; ++dx) {
-        const uint64_t wgt = c.w[0][dx] * wyz;
-        const int i = (c.cell[0] + dx) & m;
-        const double wd = (double)wgt * norm;
-        const double gx = -(phi[lin((i + 1) & m, j, k, n)] - phi[lin((i - 1) & m, j, k, n)]) * inv2h;
-        const double gy = -(phi[lin(i, jp, k, n)] - phi[lin(i, jm, k, n)]) * inv2h;
-        const double gz = -(phi[lin(i, j, kp, n)] - phi[lin(i, j, km, n)]) * inv2h;
-        g[0] += wd * gx;
-        g[1] += wd * gy;
-        g[2] += wd * gz;
+  double w[3][S], d[3][S + 2];
+#pragma unroll
+  for (int ax = 0; ax < 3; ++ax) {
+#pragma unroll
+    for (int t = 0; t < S; ++t) w[ax][t] = (double)c.w[ax][t];
+#pragma unroll
+    for (int t = 0; t < S + 2; ++t)
+      d[ax][t] = (t >= 2 ? w[ax][t >= 2 ? t - 2 : 0] : 0.0) - (t < S ? w[ax][t < S ? t : 0] : 0.0);
+  }
+  int jr[S + 2];
+#pragma unroll
+  for (int t = 0; t < S + 2; ++t) jr[t] = ((c.cell[1] - 1 + t) & m) * n;
+  const int i0 = c.cell[0] - 1;
+  const double ref = phi[lin(c.cell[0] & m, c.cell[1] & m, c.cell[2] & m, n)];
+  double gx = 0.0, gy = 0.0, gz = 0.0;
+  // rows (j, k) with both in the stencil draw on S + 2 values, those one step
+  // outside it along y or z on S
+  auto rows = [&](auto load) {
+#pragma unroll
+    for (int tz = 0; tz < S + 2; ++tz) {
+      const int64_t plane = (int64_t)((c.cell[2] - 1 + tz) & m) * n * n;
+      const bool inz = tz > 0 && tz <= S;
+#pragma unroll
+      for (int ty = 0; ty < S + 2; ++ty) {
+        const bool iny = ty > 0 && ty <= S;
+        if (!inz && !iny) continue;
+        double v[S + 2];
+        load(phi + plane + jr[ty], inz && iny, v);
+        double sw = 0.0, sd = 0.0;
+#pragma unroll
+        for (int t = 0; t < S; ++t) sw += w[0][t] * (v[t + 1] - ref);
+        if (inz && iny) {
+#pragma unroll
+          for (int t = 0; t < S + 2; ++t) sd += d[0][t] * (v[t] - ref);
+          gx += sd * (w[1][iny ? ty - 1 : 0] * w[2][inz ? tz - 1 : 0]);
+        }
+        if (inz) gy += sw * (d[1][ty] * w[2][inz ? tz - 1 : 0]);
+        if (iny) gz += sw * (w[1][iny ? ty - 1 : 0] * d[2][tz]);
       }
     }
+  };
+  if (!__any(i0 < 0 || i0 + S + 1 >= n)) {
+    // no row of the wave's particles wraps around
+    typedef double f64x2 __attribute__((ext_vector_type(2), aligned(8)));
+    rows([&](const double* row, bool wide, double (&v)[S + 2]) {
+      const int first = wide ? 0 : 1, count = wide ? S + 2 : S;
+#pragma unroll
+      for (int t = 0; t < S + 2; t += 2) {
+        if (t + 2 <= count) {
+          const f64x2 x = *(const f64x2*)(row + i0 + first + t);
+          v[first + t] = x[0];
+          v[first + t + 1] = x[1];
+        } else if (t < count) {
+          v[first + t] = row[i0 + first + t];
+        }
+      }
+    });
+  } else {
+    rows([&](const double* row, bool wide, double (&v)[S + 2]) {
+#pragma unroll
+      for (int t = 0; t < S + 2; ++t)
+        if (wide || (t > 0 && t <= S)) v[t] = row[(i0 + t) & m];
+    });
   }
+  const double norm = -inv2h * ldexp(1.0, -3 * mm.frac_bits);
+  g[0] = gx * norm;
+  g[1] = gy * norm;
+  g[2] = gz * norm;
 }
 
 // The same from the FP32 force mesh g3 (3 values per cell): one 12-byte
