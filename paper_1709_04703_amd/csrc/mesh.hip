@@ -1557,6 +1557,124 @@ k_coarse(T* __restrict__ e, const T* __restrict__ r, int n, Box b, T scale, T in
       if (has[c][u]) e[gidx[c][u]] = es[own[c][u]] - emean;
 }
 
+// cos(2 pi m / 16)
+__device__ inline double cos16(int m) {
+  m &= 15;
+  const int t = m > 8 ? 16 - m : m, u = t > 4 ? 8 - t : t;
+  const double v = u == 0   ? 1.0
+                   : u == 1 ? 0.92387953251128675613    // cos(pi / 8)
+                   : u == 2 ? 0.70710678118654752440    // sqrt(1 / 2)
+                   : u == 3 ? 0.38268343236508977173    // sin(pi / 8)
+                            : 0.0;
+  return t > 4 ? -v : v;
+}
+
+// The same on the periodic level of 16^3 cells, mode by mode: the products of
+// (cos + sin)(2 pi k x / 16) over the axes diagonalise the neighbour sum, with
+// lam = 2 (cos kx + cos ky + cos kz), and k + (8, 8, 8) is the mode k with its
+// black cells negated.  With R, B the amplitudes of such a pair on the red and
+// black cells, mu = lam inv_diag and s = scale inv_diag, a sweep is
+//   R <- mu B - s r_R,  B <- mu R - s r_B = mu^2 B - s (mu r_R + r_B),
+// a geometric sum after `sweeps` of them, so their number costs a few
+// products (the sum's partial sums by doubling, which also holds at mu = 1).
+// Removing the means of r and e is setting the constant mode to 0.
+// The transforms are products by the symmetric 16 x 16 matrix
+// h_kx = (cos + sin)(2 pi k x / 16) / 4, its own inverse, on the FP64 matrix
+// instruction for FP32 levels as well.  A wave takes planes z = w, w + 8 in x
+// and y, then rows ky = w, w + 8 in z.  A product's result lies in the
+// registers as the next one's operand (lane l, element q: row l / 16 + 4 q,
+// column l % 16, of the result as of a right operand; the transpose as of a
+// left one), so only the turn from planes to rows and back passes through LDS
+// (rows of 17 doubles: no bank conflicts either way).
+// Bound by latency and by the 48 matrix instructions of each wave: 9 us whatever
+// the sweeps (64 of them in k_coarse: 45 us in FP32, 48 in FP64).
+template <typename T>
+__global__ void __launch_bounds__(512)
+k_coarse_modes(T* __restrict__ e, const T* __restrict__ r, T scale, T inv_diag, int sweeps,
+               int project) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  constexpr int kRow = 17, kPlane = 16 * kRow;
+  __shared__ double S[16 * kPlane];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, col = l & 15, row = l >> 4;
+  f64x4 f[2], h, sum;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[t][q] = (double)r[sidx(col, row + 4 * q, w + 8 * t, 16)];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int a = (row + 4 * q) * col;
+    h[q] = 0.25 * (cos16(a) + cos16(a - 4));
+  }
+  // mu and 1 + mu^2 + ... (sweeps - 1 terms) of the modes (col, w, row + 4 q)
+  double mu[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    mu[q] = 2.0 * (cos16(col) + cos16(w) + cos16(row + 4 * q)) * (double)inv_diag;
+    const double m2 = mu[q] * mu[q];
+    double acc = 0.0, pw = 1.0;
+    for (int bit = 31 - __clz(sweeps); bit >= 0; --bit) {
+      acc += acc * pw;
+      pw *= pw;
+      if ((sweeps - 1) >> bit & 1) {
+        acc += pw;
+        pw *= m2;
+      }
+    }
+    sum[q] = acc;
+  }
+  // d += A B of 16 x 16 matrices
+  auto mul = [](f64x4 a, f64x4 b) {
+    f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) d = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], d, 0, 0, 0);
+    return d;
+  };
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    f[t] = mul(f[t], h);                         // (x, ky)
+    f[t] = mul(h, f[t]);                         // (kx, ky)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S[(w + 8 * t) * kPlane + col * kRow + row + 4 * q] = f[t][q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[t][q] = S[(row + 4 * q) * kPlane + (w + 8 * t) * kRow + col];
+    f[t] = mul(h, f[t]);                         // (kz, kx)
+  }
+  // mode (col, w, row + 4 q) of f[0]; its partner is f[1][q ^ 2] of lane l ^ 8
+  const bool zero_mode = project && threadIdx.x == 0;
+  const double s = (double)scale * (double)inv_diag;
+  f64x4 g[2];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double a = zero_mode && q == 0 ? 0.0 : f[0][q], b = __shfl_xor(f[1][q ^ 2], 8);
+    const double rr = a + b, rb = a - b;
+    const double c = -s * (mu[q] * rr + rb);
+    const double er = mu[q] * c * sum[q] - s * rr, eb = c * (1.0 + mu[q] * mu[q] * sum[q]);
+    g[0][q] = zero_mode && q == 0 ? 0.0 : 0.5 * (er + eb);
+    g[1][q ^ 2] = __shfl_xor(0.5 * (er - eb), 8);
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    f[t] = mul(h, g[t]);                         // (z, kx)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S[(row + 4 * q) * kPlane + (w + 8 * t) * kRow + col] = f[t][q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[t][q] = S[(w + 8 * t) * kPlane + col * kRow + row + 4 * q];
+    f[t] = mul(f[t], h);                         // (ky, x)
+    f[t] = mul(h, f[t]);                         // (y, x)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) e[sidx(col, row + 4 * q, w + 8 * t, 16)] = (T)f[t][q];
+  }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_residual_guess(const double* __restrict__ phi, const float* __restrict__ d, double scale,
@@ -2387,7 +2505,7 @@ static int sweeps_for_1e3(const Level& L, int l, double kappa, bool periodic) {
 }
 
 // Levels whose way down and way up are one launch each (tile.hip): V(2,2)
-// cycles on meshes of up to 128^3.  The profiler charges their time to the
+// cycles, on levels of up to 64^3 cells.  The profiler charges their time to the
 // half sweeps in them (all but a red one from zero), with the bytes of as many
 // separate half sweeps.
 constexpr int kTileMax = 64;
@@ -2395,6 +2513,10 @@ static bool tiles(const Level& L, int pre, int post) { return pre == 2 && post =
 // whether the separate kernels would take their 4-cell forms on this level
 template <typename T>
 static bool v4_level(const Level& L) { return sizeof(T) == 4 && v4_threads(L.box) != 0; }
+
+// Sweeps from which the periodic 16^3 level is solved mode by mode: 7 of them take
+// k_coarse 9.5 us in FP32 and 10 in FP64, k_coarse_modes takes 9.
+constexpr int kModesMin = 8;
 
 template <typename T>
 const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int coarse_sweeps,
@@ -2452,7 +2574,12 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
                                   (int64_t)kCoarseMax * kCoarseMax * kCoarseMax);
     const T scale = (T)sc, inv_diag = (T)(1.0 / (6.0 + sc * kappa));
     const int sweeps = std::max(1, std::min(coarse_sweeps, sweeps_for_1e3(L, l, kappa, periodic)));
-    if (fits) {
+    if (periodic && L.n == 16 && sweeps >= kModesMin) {
+      prof_begin(st, K_COARSE);
+      hipLaunchKernelGGL(k_coarse_modes<T>, dim3(1), dim3(512), 0, st, (T*)L.e, (const T*)L.r, scale,
+                         inv_diag, sweeps, kappa == 0.0 ? 1 : 0);
+      prof_end(st, K_COARSE, 2 * es * (double)box_cells(L.box));
+    } else if (fits) {
       prof_begin(st, K_COARSE);
       hipLaunchKernelGGL(k_coarse<T>, dim3(1), dim3(1024), 0, st, (T*)L.e, (const T*)L.r, L.n,
                          L.box, scale, inv_diag, sweeps,
