@@ -204,7 +204,7 @@ k_residual(const double* __restrict__ phi, const double* __restrict__ rhs, T* __
 // k_residual with 4 consecutive cells per thread (vector loads of phi and
 // rhs, two 2-wide stores per colour of r).  Vectors start at multiples of 4
 // (the box's first x index rounded down); cells outside the box are masked.
-// A tile is 4 TXV cells x 256 / TXV rows x kResKz planes.
+// A tile is 4 TXV cells x 256 / TXV rows x kz planes (res_planes).
 #ifndef SDPM_RES_KZ
 #define SDPM_RES_KZ 16
 #endif
@@ -213,12 +213,24 @@ k_residual(const double* __restrict__ phi, const double* __restrict__ rhs, T* __
 // least as many cells as the box kernels', whose grid sizes the reduction
 // partials
 constexpr int kResKz = SDPM_RES_KZ;
-static_assert(kResKz >= 2, "more residual workgroups than reduction partials");
+// Fewer planes, down to two, where they leave less than kResGrid workgroups:
+// a march is a serial chain of loads, and a small mesh has too few of them to
+// hide it (128^3 in FP32, 4 planes instead of 16: correction with
+// estimate 34 -> 18 us, source and residual 30 -> 16 us; 32^3 in FP64: 31 -> 8 us;
+// 256 workgroups: 22 and 20 us at 128^3, 1024: 16 and 17).
+constexpr int kResKzMin = 2, kResGrid = 512;
+static_assert(kResKzMin >= 2 && kResKz >= kResKzMin, "more residual workgroups than reduction partials");
+// cols: tiles in x and y
+static int res_planes(unsigned cols, const Box& b) {
+  int kz = kResKz;
+  while (kz > kResKzMin && cols * (unsigned)((b.hi[2] - b.lo[2] + kz) / kz) < kResGrid) kz >>= 1;
+  return kz;
+}
 
 template <typename T, int TXV>
 __global__ void __launch_bounds__(256)
 k_residual_v4(const double* __restrict__ phi, const double* __restrict__ rhs, T* __restrict__ rout,
-              int n, Box b, double kappa, double* __restrict__ partial) {
+              int n, Box b, double kappa, double* __restrict__ partial, int kz) {
   __shared__ double sh[4];
   constexpr int TY = 256 / TXV;
   const int ib = b.lo[0] & ~3;
@@ -228,8 +240,8 @@ k_residual_v4(const double* __restrict__ phi, const double* __restrict__ rhs, T*
   const int m = n - 1;
   double acc = 0.0;
   if (i0 <= b.hi[0] && j <= b.hi[1]) {
-    const int k0 = b.lo[2] + tl.bz * kResKz;
-    const int k1 = min(k0 + kResKz - 1, b.hi[2]);
+    const int k0 = b.lo[2] + tl.bz * kz;
+    const int k1 = min(k0 + kz - 1, b.hi[2]);
     const int jp = (j + 1) & m, jm = (j - 1) & m, il = (i0 - 1) & m, ir = (i0 + 4) & m;
     const bool full = i0 >= b.lo[0] && i0 + 3 <= b.hi[0];
     const bool lane_l = threadIdx.x > 0, lane_r = threadIdx.x + 1 < TXV && i0 + 4 <= b.hi[0];
@@ -315,7 +327,7 @@ k_rhs_residual_v4(const uint64_t* __restrict__ counts, const double* __restrict_
                   double* __restrict__ rhs, T* __restrict__ rout, float* __restrict__ chg, int n,
                   Box b, double c_scale, double c_off, double kappa, double chg_scale,
                   int nblocks, double* __restrict__ partial, float* __restrict__ g3,
-                  double inv2h) {
+                  double inv2h, int kz) {
   __shared__ double sh[4];
   __shared__ __attribute__((aligned(16))) float stage[FORCE ? 12 * 256 : 4];
   constexpr int TY = 256 / TXV;
@@ -342,8 +354,8 @@ k_rhs_residual_v4(const uint64_t* __restrict__ counts, const double* __restrict_
     return MODE == 2 ? v + (double)(float)(chg_scale * (double)chg[c]) : v;
   };
   if (i0 <= b.hi[0] && j <= b.hi[1]) {
-    const int k0 = b.lo[2] + tl.bz * kResKz;
-    const int k1 = min(k0 + kResKz - 1, b.hi[2]);
+    const int k0 = b.lo[2] + tl.bz * kz;
+    const int k1 = min(k0 + kz - 1, b.hi[2]);
     const int jp = (j + 1) & m, jm = (j - 1) & m, il = (i0 - 1) & m, ir = (i0 + 4) & m;
     const bool full = i0 >= b.lo[0] && i0 + 3 <= b.hi[0];
     const bool lane_l = threadIdx.x > 0, lane_r = threadIdx.x + 1 < TXV && i0 + 4 <= b.hi[0];
@@ -550,7 +562,7 @@ k_correct(double* __restrict__ phi, const T* __restrict__ e, float* __restrict__
 // the new phi and of e (slots 0..3), from which the host bounds the
 // distance between the estimate and the FP64 residual.  Tiles as in
 // k_residual_v4: 4 consecutive cells per lane (i0 a multiple of 4), a row
-// segment over the TXV lanes of a wave, kResKz planes walked with e of
+// segment over the TXV lanes of a wave, kz planes walked with e of
 // planes k - 1, k, k + 1 in registers; e and r_old of the lane's cells are
 // two 2-wide loads per colour-split row (cells i0, i0 + 2 and i0 + 1,
 // i0 + 3), its x neighbours the adjacent lanes' end cells.
@@ -558,7 +570,7 @@ template <typename T, int TXV, bool CHG, bool PENDING>
 __global__ void __launch_bounds__(256)
 k_correct_est_v4(double* __restrict__ phi, const T* __restrict__ e, const T* __restrict__ rold,
                  float* __restrict__ chg, int n, Box b, double chg_scale, double kappa,
-                 double* __restrict__ partial) {
+                 double* __restrict__ partial, int kz) {
   __shared__ double sh[4];
   constexpr int TY = 256 / TXV;
   const int ib = b.lo[0] & ~3;
@@ -598,8 +610,8 @@ k_correct_est_v4(double* __restrict__ phi, const T* __restrict__ e, const T* __r
     for (int q = 0; q < 4; ++q) r.v[q] = (T)0;
     return r;
   };
-  const int k0 = b.lo[2] + tl.bz * kResKz;
-  const int k1 = min(k0 + kResKz - 1, b.hi[2]);
+  const int k0 = b.lo[2] + tl.bz * kz;
+  const int k1 = min(k0 + kz - 1, b.hi[2]);
   double s_est = 0.0, s_old = 0.0, s_phi = 0.0, s_e = 0.0;
   Vec4<T> below = zero4(), ctr = zero4();
   if (in) {
@@ -1838,18 +1850,19 @@ void launch_residual(const double* phi, const double* rhs, T* r_out, int n, cons
     const int txv = tile_threads(b.hi[0] - ib + 1);
     const unsigned gx = (unsigned)((b.hi[0] - ib + 4 * txv) / (4 * txv));
     const unsigned gy = (unsigned)((b.hi[1] - b.lo[1] + 256 / txv) / (256 / txv));
-    const unsigned gz = (unsigned)((b.hi[2] - b.lo[2] + kResKz) / kResKz);
+    const int kz = res_planes(gx * gy, b);
+    const unsigned gz = (unsigned)((b.hi[2] - b.lo[2] + kz) / kz);
     *nblocks = (int)(gx * gy * gz);
     const dim3 g(gx * gy * gz), blk(txv, 256 / txv);
     if (txv == 64)
       hipLaunchKernelGGL((k_residual_v4<T, 64>), g, blk, 0, st, phi, rhs, r_out, n, b, kappa,
-                         partial);
+                         partial, kz);
     else if (txv == 32)
       hipLaunchKernelGGL((k_residual_v4<T, 32>), g, blk, 0, st, phi, rhs, r_out, n, b, kappa,
-                         partial);
+                         partial, kz);
     else
       hipLaunchKernelGGL((k_residual_v4<T, 16>), g, blk, 0, st, phi, rhs, r_out, n, b, kappa,
-                         partial);
+                         partial, kz);
   } else {
     const dim3 g = box_grid(b);
     *nblocks = (int)(g.x * g.y * g.z);
@@ -2022,17 +2035,17 @@ template void launch_correct<double>(double*, const double*, float*, double, int
 template <typename T, int TXV>
 static void correct_est_tiles(double* phi, const T* e, const T* r_old, float* chg,
                               double pending_scale, double kappa, int n, const Box& b,
-                              double* partial, const dim3& g, hipStream_t st) {
+                              double* partial, const dim3& g, int kz, hipStream_t st) {
   const dim3 blk(TXV, 256 / TXV);
   if (chg && pending_scale != 0.0)
     hipLaunchKernelGGL((k_correct_est_v4<T, TXV, true, true>), g, blk, 0, st, phi, e, r_old, chg, n,
-                       b, pending_scale, kappa, partial);
+                       b, pending_scale, kappa, partial, kz);
   else if (chg)
     hipLaunchKernelGGL((k_correct_est_v4<T, TXV, true, false>), g, blk, 0, st, phi, e, r_old, chg,
-                       n, b, 0.0, kappa, partial);
+                       n, b, 0.0, kappa, partial, kz);
   else
     hipLaunchKernelGGL((k_correct_est_v4<T, TXV, false, false>), g, blk, 0, st, phi, e, r_old,
-                       nullptr, n, b, 0.0, kappa, partial);
+                       nullptr, n, b, 0.0, kappa, partial, kz);
 }
 
 template <typename T>
@@ -2045,16 +2058,20 @@ void launch_correct_est(double* phi, const T* e, const T* r_old, float* chg, dou
   const int txv = tile_threads(b.hi[0] - ib + 1);
   const unsigned gx = (unsigned)((b.hi[0] - ib + 4 * txv) / (4 * txv));
   const unsigned gy = (unsigned)((b.hi[1] - b.lo[1] + 256 / txv) / (256 / txv));
-  const unsigned gz = (unsigned)((b.hi[2] - b.lo[2] + kResKz) / kResKz);
+  const int kz = res_planes(gx * gy, b);
+  const unsigned gz = (unsigned)((b.hi[2] - b.lo[2] + kz) / kz);
   const dim3 g(gx * gy * gz);
   *nblocks = (int)g.x;
   prof_begin(st, K_CORRECT_EST);
   if (txv == 64)
-    correct_est_tiles<T, 64>(phi, e, r_old, chg, pending_scale, kappa, n, b, partial, g, st);
+    correct_est_tiles<T, 64>(phi, e, r_old, chg, pending_scale, kappa, n, b, partial, g, kz,
+                              st);
   else if (txv == 32)
-    correct_est_tiles<T, 32>(phi, e, r_old, chg, pending_scale, kappa, n, b, partial, g, st);
+    correct_est_tiles<T, 32>(phi, e, r_old, chg, pending_scale, kappa, n, b, partial, g, kz,
+                              st);
   else
-    correct_est_tiles<T, 16>(phi, e, r_old, chg, pending_scale, kappa, n, b, partial, g, st);
+    correct_est_tiles<T, 16>(phi, e, r_old, chg, pending_scale, kappa, n, b, partial, g, kz,
+                              st);
   prof_end(st, K_CORRECT_EST, (16.0 + 2.0 * sizeof(T) + (chg ? 8.0 : 0.0)) * box_cells(b));
 }
 template void launch_correct_est<float>(double*, const float*, const float*, float*, double,
@@ -2084,7 +2101,8 @@ bool launch_rhs_residual(const uint64_t* counts, const double* phi, double* rhs,
   const int txv = tile_threads(b.hi[0] - ib + 1);
   const unsigned gx = (unsigned)((b.hi[0] - ib + 4 * txv) / (4 * txv));
   const unsigned gy = (unsigned)((b.hi[1] - b.lo[1] + 256 / txv) / (256 / txv));
-  const unsigned gz = (unsigned)((b.hi[2] - b.lo[2] + kResKz) / kResKz);
+  const int kz = res_planes(gx * gy, b);
+  const unsigned gz = (unsigned)((b.hi[2] - b.lo[2] + kz) / kz);
   const int nb = (int)(gx * gy * gz);
   *nblocks = nb;
   const dim3 g(gx * gy * gz), blk(txv, 256 / txv);
@@ -2093,7 +2111,7 @@ bool launch_rhs_residual(const uint64_t* counts, const double* phi, double* rhs,
   prof_begin(st, force ? K_RHS_FORCE : K_RHS);
 #define SDPM_RR(TX, M, F)                                                                        \
   hipLaunchKernelGGL((k_rhs_residual_v4<T, TX, M, F>), g, blk, 0, st, counts, phi, rhs, r_out,   \
-                     chg, n, b, c_scale, c_off, kappa, chg_scale, nb, partial, g3, inv2h)
+                     chg, n, b, c_scale, c_off, kappa, chg_scale, nb, partial, g3, inv2h, kz)
 #define SDPM_RR_TX(M, F)                                                                         \
   if (txv == 64) SDPM_RR(64, M, F); else if (txv == 32) SDPM_RR(32, M, F); else SDPM_RR(16, M, F)
   if (force) {
