@@ -215,23 +215,23 @@ void launch_tile_up(const Level& L, const Level& C, int l, double kappa, bool pe
 template <typename T>
 void launch_tile_sweeps(const Level& L, int l, double kappa, bool periodic, int sweeps,
                         hipStream_t st);
-// Whether a level of n cells a side takes the fused four-sweep kernel (FP32
-// only; smaller levels run too few workgroups for it).
+// Cells a side from which a level takes the fused four-sweep kernel (smaller
+// levels run too few workgroups for it).
 constexpr int kSweep4Min = 256;
-// Four colour sweeps (red, black, red, black) of a periodic FP32 level of
-// n^3 cells, n a power of two >= 64: with fused, one k_sweep4 pass from e
+// Four colour sweeps (red, black, red, black) of a periodic level of n^3 cells, n a power of two >= 64: with fused, one k_sweep4 pass from e
 // (black colour; not read when first) into e_out (e_out == e allowed only
 // when first); otherwise e copied to e_out (not when first) and four
 // k_smooth_color_v4 launches in place on e_out.  With t (may be null) the
 // red residual of the result goes to t's red half (inv_scale = 1 / scale,
 // kappa = kappa h^2): in the fused pass instead of the red half of e_out,
 // which it then leaves unwritten; otherwise by k_resid_red_v4.
+// The fused pass of an FP64 level takes no t.
 // With box (may be null: the periodic whole mesh) the sweeps cover a
 // frozen-exterior box that keeps at least one plane from every face of the
 // mesh, e being zero outside it.
-void launch_sweeps4(const float* e, float* e_out, const float* r, int n, float scale, float inv_diag,
-                    bool first, bool fused, float* t, float inv_scale, float kappa, const Box* box,
-                    hipStream_t st);
+template <typename T>
+void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag, bool first,
+                    bool fused, T* t, T inv_scale, T kappa, const Box* box, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Launchers, particle kernels (particles.hip).

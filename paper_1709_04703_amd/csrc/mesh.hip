@@ -879,9 +879,10 @@ k_smooth_color_v4(T* __restrict__ eo, const T* __restrict__ ex, const T* __restr
   }
 }
 
-// Four colour sweeps (red, black, red, black) of a periodic FP32 level in
-// one pass, with the arithmetic of four k_smooth_color_v4 launches (same
-// operands, same order: bit-identical results).  Four separate sweeps move
+// Four colour sweeps (red, black, red, black) of a level in one pass, with the
+// arithmetic of four k_smooth_color_v4 (in FP64 k_smooth_color) launches (same
+// operands, same order: bit-identical results).  The figures are of FP32 levels
+// unless they say otherwise.  Four separate sweeps move
 // 24 bytes per cell (each half sweep reads the other colour and its own r,
 // writes its own colour); here each cell's r and input black value are read
 // once and its final red and black values written once: 10 bytes per cell
@@ -921,6 +922,11 @@ k_smooth_color_v4(T* __restrict__ eo, const T* __restrict__ ex, const T* __restr
 // ring keeps one more plane (7), the halo one more row, and the first
 // sweep takes the black input just outside the region in x from ldsx.
 //
+// FP64: an LDS plane is twice as large, which leaves room for 64 x 32-cell
+// columns without the residual's stage (154 KB).  256^3: 97 us per pass, 76
+// from zero, against 172 and 154 in separate sweeps (which move 48 bytes a cell
+// at the rate of a copy); FP64 step on 256^3 with TSC 5.53 -> 4.51 ms.
+//
 // Requires n a power of two >= 8 UX, n % zc == 0.  FIRST: the red sweep starts
 // from e = 0 and ein is not read (eout may be the level's e); otherwise ein
 // supplies the black colour and must not alias eout (other workgroups still
@@ -930,10 +936,10 @@ struct StepPhase {
   static constexpr int value = V;
 };
 
-template <bool FIRST, bool RES, bool BOX, int UX, int TY, int NT>
+template <typename T, bool FIRST, bool RES, bool BOX, int UX, int TY, int NT>
 __global__ void __launch_bounds__(NT)
-k_sweep4(const float* __restrict__ ein, float* __restrict__ eout, const float* __restrict__ r, int n,
-         int zc, float scale, float inv_diag, float* __restrict__ tout, float inv_scale, float kappa,
+k_sweep4(const T* __restrict__ ein, T* __restrict__ eout, const T* __restrict__ r, int n,
+         int zc, T scale, T inv_diag, T* __restrict__ tout, T inv_scale, T kappa,
          Box b) {
   constexpr int G = RES ? 1 : 0;                 // the residual: one more stage
   constexpr int HY = 4 + G;                      // halo rows per side
@@ -941,9 +947,9 @@ k_sweep4(const float* __restrict__ ein, float* __restrict__ eout, const float* _
   constexpr int ITEMS = RY * U;
   static_assert(ITEMS <= NT, "one region unit per thread");
   constexpr int L = 6, NS = 6, NB = NS + G, D = L - 3;   // queue length = unroll = red LDS slots
-  __shared__ __align__(16) float ldsb[NB * PL];
-  __shared__ __align__(16) float ldsr[NS * PL];
-  __shared__ float ldsx[RES ? NB * 2 * RY : 1];   // black input just outside the region in x
+  __shared__ __align__(16) T ldsb[NB * PL];
+  __shared__ __align__(16) T ldsr[NS * PL];
+  __shared__ T ldsx[RES ? NB * 2 * RY : 1];   // black input just outside the region in x
   const int hn = n >> 1, m = n - 1, hm = hn - 1;
   const int64_t oth = (int64_t)n * n * hn, pls = (int64_t)n * hn;
   // columns over the mesh, or with BOX over the box (from its first
@@ -964,21 +970,21 @@ k_sweep4(const float* __restrict__ ein, float* __restrict__ eout, const float* _
   // faces, so a wrapped index always lies outside it)
   const int hu = H0 - 4 + 4 * u, ju = Y0 - HY + y;
   const bool rowin = !BOX || (ju >= b.lo[1] && ju <= b.hi[1]);
-  auto mask = [&](int c, int z, int h, Vec4<float>& v) {
+  auto mask = [&](int c, int z, int h, Vec4<T>& v) {
     if constexpr (BOX) {
       const bool in = rowin && z >= b.lo[2] && z <= b.hi[2];
       const int p = (c + jj + (z & m)) & 1;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         const int x = 2 * (h + w) + p;
-        if (!(in && x >= b.lo[0] && x <= b.hi[0])) v.v[w] = 0.f;
+        if (!(in && x >= b.lo[0] && x <= b.hi[0])) v.v[w] = (T)0;
       }
     }
   };
-  auto mask1 = [&](int c, int z, int h, float& v) {   // one entry at half index h
+  auto mask1 = [&](int c, int z, int h, T& v) {   // one entry at half index h
     if constexpr (BOX) {
       const int x = 2 * h + ((c + jj + (z & m)) & 1);
-      if (!(rowin && z >= b.lo[2] && z <= b.hi[2] && x >= b.lo[0] && x <= b.hi[0])) v = 0.f;
+      if (!(rowin && z >= b.lo[2] && z <= b.hi[2] && x >= b.lo[0] && x <= b.hi[0])) v = (T)0;
     }
   };
   const int jh = jj * hn + ((H0 - 4 + 4 * u) & hm);   // row and half index of the unit
@@ -1003,74 +1009,77 @@ k_sweep4(const float* __restrict__ ein, float* __restrict__ eout, const float* _
   // qe (and its value outside the region in qx); with RES the residual's r,
   // red result and the black results of the two planes next to it in q5r,
   // q3, q4 (indexed by plane mod 3)
-  Vec4<float> qr[L], qb[L], qe[L];
-  float qx[RES ? L : 1];
-  Vec4<float> q5r[RES ? 3 : 1], q3[RES ? 3 : 1], q4[RES ? 3 : 1];
+  Vec4<T> qr[L], qb[L], qe[L];
+  T qx[RES ? L : 1];
+  Vec4<T> q5r[RES ? 3 : 1], q3[RES ? 3 : 1], q4[RES ? 3 : 1];
   const int zs = Z0 - 3 - G, ze = Z0 + zc + 2 + G;
-  auto ld_r = [&](int c, int z) { return *(const Vec4<float>*)(r + c * oth + (int64_t)(z & m) * pls + jh); };
-  auto ld_e = [&](int z) { return *(const Vec4<float>*)(ein + oth + (int64_t)(z & m) * pls + jh); };
+  auto ld_r = [&](int c, int z) { return *(const Vec4<T>*)(r + c * oth + (int64_t)(z & m) * pls + jh); };
+  auto ld_e = [&](int z) { return *(const Vec4<T>*)(ein + oth + (int64_t)(z & m) * pls + jh); };
   auto ld_x = [&](int z) { return ein[oth + (int64_t)(z & m) * pls + jx]; };
   // colour c on plane z, rows [lo, RY - lo): s* = the other colour's planes
   // z - 1, z, z + 1; the result goes to ov and (keep) to dst
-  auto sweep = [&](int c, int z, const float* sm, const float* s0, const float* sp, float* dst, int lo,
-                   bool zero, const Vec4<float>& rv, bool keep, Vec4<float>& ov, const float* sx) {
+  auto sweep = [&](int c, int z, const T* sm, const T* s0, const T* sp, T* dst, int lo,
+                   bool zero, const Vec4<T>& rv, bool keep, Vec4<T>& ov, const T* sx) {
     if (!ok || y < lo || y >= RY - lo) return;
     const int p = (c + jj + (z & m)) & 1;   // cell q of the unit: x = 2 (h0 + q) + p
     if (zero) {
 #pragma unroll
       for (int w = 0; w < 4; ++w) ov.v[w] = -scale * rv.v[w] * inv_diag;
     } else {
-      const Vec4<float> xc = *(const Vec4<float>*)(s0 + base);
-      const Vec4<float> ym = *(const Vec4<float>*)(s0 + base - HW);
-      const Vec4<float> yp = *(const Vec4<float>*)(s0 + base + HW);
-      const Vec4<float> zm = *(const Vec4<float>*)(sm + base);
-      const Vec4<float> zp = *(const Vec4<float>*)(sp + base);
-      float xs = s0[p ? xhi : xlo];
+      const Vec4<T> xc = *(const Vec4<T>*)(s0 + base);
+      const Vec4<T> ym = *(const Vec4<T>*)(s0 + base - HW);
+      const Vec4<T> yp = *(const Vec4<T>*)(s0 + base + HW);
+      const Vec4<T> zm = *(const Vec4<T>*)(sm + base);
+      const Vec4<T> zp = *(const Vec4<T>*)(sp + base);
+      T xs = s0[p ? xhi : xlo];
       if (sx && (p ? edge_r : edge_l)) xs = sx[(p ? RY : 0) + y];
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         // x neighbours: xc[w] and the one on the p side, in this order
         // (k_smooth_color_v4 adds them the other way round for p = 0; the
         // sum of two floats does not depend on the order)
-        const float side = p ? (w == 3 ? xs : xc.v[w + 1]) : (w == 0 ? xs : xc.v[w - 1]);
+        const T side = p ? (w == 3 ? xs : xc.v[w + 1]) : (w == 0 ? xs : xc.v[w - 1]);
         ov.v[w] = (xc.v[w] + side + ym.v[w] + yp.v[w] + zm.v[w] + zp.v[w] - scale * rv.v[w]) * inv_diag;
       }
     }
     mask(c, z, hu, ov);
-    if (keep) *(Vec4<float>*)(dst + base) = ov;
+    if (keep) *(Vec4<T>*)(dst + base) = ov;
   };
   // red residual t = r - A e on plane z (rows [HY, RY - HY)) with the
   // arithmetic of k_resid_red_v4: black neighbours in the plane from s0, in
   // the planes next to it from bm / bp, the cell's red value ctr
-  auto resid = [&](int z, const float* s0, const Vec4<float>& bm, const Vec4<float>& bp,
-                   const Vec4<float>& ctr, const Vec4<float>& rv, Vec4<float>& ov) {
+  auto resid = [&](int z, const T* s0, const Vec4<T>& bm, const Vec4<T>& bp,
+                   const Vec4<T>& ctr, const Vec4<T>& rv, Vec4<T>& ov) {
     if (!ok || y < HY || y >= RY - HY) return;
     const int p = (jj + (z & m)) & 1;
-    const Vec4<float> xc = *(const Vec4<float>*)(s0 + base);
-    const Vec4<float> ym = *(const Vec4<float>*)(s0 + base - HW);
-    const Vec4<float> yp = *(const Vec4<float>*)(s0 + base + HW);
-    const float xs = s0[p ? xhi : xlo];
+    const Vec4<T> xc = *(const Vec4<T>*)(s0 + base);
+    const Vec4<T> ym = *(const Vec4<T>*)(s0 + base - HW);
+    const Vec4<T> yp = *(const Vec4<T>*)(s0 + base + HW);
+    const T xs = s0[p ? xhi : xlo];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float side = p ? (w == 3 ? xs : xc.v[w + 1]) : (w == 0 ? xs : xc.v[w - 1]);
-      const float nb = xc.v[w] + side + ym.v[w] + yp.v[w] + bm.v[w] + bp.v[w];
-      ov.v[w] = rv.v[w] - (nb - 6.0f * ctr.v[w]) * inv_scale + kappa * ctr.v[w];
+      const T side = p ? (w == 3 ? xs : xc.v[w + 1]) : (w == 0 ? xs : xc.v[w - 1]);
+      const T nb = xc.v[w] + side + ym.v[w] + yp.v[w] + bm.v[w] + bp.v[w];
+      ov.v[w] = rv.v[w] - (nb - (T)6 * ctr.v[w]) * inv_scale + kappa * ctr.v[w];
     }
     mask(0, z, hu, ov);
   };
-  auto put = [&](float* dst, int c, int z, bool valid, const Vec4<float>& ov) {
+  auto put = [&](T* dst, int c, int z, bool valid, const Vec4<T>& ov) {
     const __amdgpu_buffer_rsrc_t rsc = __builtin_amdgcn_make_buffer_rsrc(
-        dst + c * oth + (int64_t)(z & m) * pls, (short)0, (int)(pls * 4), 0x00020000);
+        dst + c * oth + (int64_t)(z & m) * pls, (short)0, (int)(pls * sizeof(T)), 0x00020000);
     typedef float v4f __attribute__((ext_vector_type(4)));
-    v4f d;
-    d.x = ov.v[0], d.y = ov.v[1], d.z = ov.v[2], d.w = ov.v[3];
-    const unsigned off = (valid && outp) ? (unsigned)jh * 4u : 0x80000000u;
-    __builtin_amdgcn_raw_buffer_store_b128(d, rsc, off, 0, 2 /* non-temporal */);
+    const unsigned off = (valid && outp) ? (unsigned)jh * (unsigned)sizeof(T) : 0x80000000u;
+#pragma unroll
+    for (int part = 0; part < (int)sizeof(T) / 4; ++part) {
+      v4f d;
+      __builtin_memcpy(&d, &ov.v[part * 16 / sizeof(T)], 16);
+      __builtin_amdgcn_raw_buffer_store_b128(d, rsc, off + 16u * part, 0, 2 /* non-temporal */);
+    }
   };
-  auto stage_black = [&](int z, Vec4<float> v, float vx) {
+  auto stage_black = [&](int z, Vec4<T> v, T vx) {
     if (!ok) return;
     mask(1, z, hu, v);
-    *(Vec4<float>*)(bs(z) + base) = v;
+    *(Vec4<T>*)(bs(z) + base) = v;
     if (RES && (edge_l || edge_r)) {
       mask1(1, z, edge_r ? H0 - 4 + 4 * U : H0 - 5, vx);
       xs_of(z)[(edge_r ? RY : 0) + y] = vx;
@@ -1080,7 +1089,7 @@ k_sweep4(const float* __restrict__ ein, float* __restrict__ eout, const float* _
   // zs - 2 .. zs + D - 1, black r planes zs - 3 .. zs + D - 2, black e
   // planes zs + 2 .. zs + L + 1 (all in bounds: plane indices wrap)
   if (!FIRST) {
-    for (int z = zs - 1; z <= zs + 1; ++z) stage_black(z, ld_e(z), RES ? ld_x(z) : 0.f);
+    for (int z = zs - 1; z <= zs + 1; ++z) stage_black(z, ld_e(z), RES ? ld_x(z) : (T)0);
   }
 #pragma unroll
   for (int x = -2; x < D; ++x) qr[(x + L) % L] = ld_r(0, zs + x);
@@ -1111,15 +1120,15 @@ k_sweep4(const float* __restrict__ ein, float* __restrict__ eout, const float* _
     using P2 = StepPhase<2>;
     // the black input of plane z + 2: into its slot now, or with RES at the
     // end of the step (its slot holds the residual's plane until then)
-    Vec4<float> hold;
-    float holdx = 0.f;
+    Vec4<T> hold;
+    T holdx = (T)0;
     if (!FIRST) {
       hold = qe[(P + 2) % L];
       if constexpr (RES) holdx = qx[(P + 2) % L];
       if (!RES && ok && z <= ze) {
-        Vec4<float> v = hold;
+        Vec4<T> v = hold;
         mask(1, z + 2, hu, v);
-        *(Vec4<float>*)(B(P2{}) + base) = v;
+        *(Vec4<T>*)(B(P2{}) + base) = v;
       }
       qe[(P + 2) % L] = ld_e(z + 2 + L);
       if constexpr (RES) qx[(P + 2) % L] = ld_x(z + 2 + L);
@@ -1127,7 +1136,7 @@ k_sweep4(const float* __restrict__ ein, float* __restrict__ eout, const float* _
     if constexpr (RES) q5r[P % 3] = qr[(P - 2 + L) % L];   // red r of plane z - 2, for step z + 2
     qr[(P + D) % L] = ld_r(0, z + D);
     qb[(P + D - 1 + L) % L] = ld_r(1, z - 1 + D);
-    Vec4<float> o1, o2, o3, o4, o5;
+    Vec4<T> o1, o2, o3, o4, o5;
     // sweep k (k = 1..4) on plane z - k + 1 for planes in
     // [Z0 - 4 - G + k, Z0 + zc + 3 + G - k]
     if (z <= ze) sweep(0, z, B(M1{}), B(Z{}), B(P1{}), R(Z{}), 1, FIRST, qr[P % L], true, o1,
@@ -2322,9 +2331,9 @@ static int sweep4_chunk(int cols, int nz) {
 
 static Box whole_mesh(int n) { return Box{{0, 0, 0}, {n - 1, n - 1, n - 1}}; }
 
-void launch_sweeps4(const float* e, float* e_out, const float* r, int n, float scale, float inv_diag,
-                    bool first, bool fused, float* t, float inv_scale, float kappa, const Box* box,
-                    hipStream_t st) {
+template <typename T>
+void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag, bool first,
+                    bool fused, T* t, T inv_scale, T kappa, const Box* box, hipStream_t st) {
   const Box b = box ? *box : whole_mesh(n);
   if (fused) {
     // 128 x 32-cell columns (one 768-thread workgroup per compute unit: 138
@@ -2335,7 +2344,7 @@ void launch_sweeps4(const float* e, float* e_out, const float* r, int n, float s
     // of 128-cell columns are short (shrinking phase at 512^3:
     // 11.5 against 11.7 ms per step; on the periodic 256^3 level the wide
     // columns win, 0.72 against 0.86 ms per step)
-    const int tx = (n >= 128 && !box) || n >= 512 ? 128 : 64;
+    const int tx = sizeof(T) == 4 && ((n >= 128 && !box) || n >= 512) ? 128 : 64;
     const int ux = tx / 8;
     const int hb = box ? ((b.lo[0] >> 1) & ~3) : 0;
     const int gx = box ? ((b.hi[0] >> 1) - hb + 4 * ux) / (4 * ux) : n / tx;
@@ -2344,7 +2353,7 @@ void launch_sweeps4(const float* e, float* e_out, const float* r, int n, float s
     const int zc = sweep4_chunk(gx * gy, nz);
     const dim3 g((unsigned)(gx * gy * ((nz + zc - 1) / zc)));
 #define SDPM_SWEEP4(F, RS, BX, UXX, NTT)                                                              \
-  hipLaunchKernelGGL((k_sweep4<F, RS, BX, UXX, 32, NTT>), g, dim3(NTT), 0, st, e, e_out, r, n, zc,    \
+  hipLaunchKernelGGL((k_sweep4<T, F, RS, BX, UXX, 32, NTT>), g, dim3(NTT), 0, st, e, e_out, r, n, zc,    \
                      scale, inv_diag, t, inv_scale, kappa, b)
 #define SDPM_SWEEP4_W(BX, UXX, NTT)               \
   do {                                            \
@@ -2357,7 +2366,20 @@ void launch_sweeps4(const float* e, float* e_out, const float* r, int n, float s
     else                                          \
       SDPM_SWEEP4(false, false, BX, UXX, NTT);    \
   } while (0)
-    if (tx == 128) {
+    if constexpr (sizeof(T) == 8) {
+      // no room for the residual's planes in LDS: 64 x 32-cell columns take 154 KB
+      // without them
+      if (box) {
+        if (first)
+          SDPM_SWEEP4(true, false, true, 8, 448);
+        else
+          SDPM_SWEEP4(false, false, true, 8, 448);
+      } else if (first) {
+        SDPM_SWEEP4(true, false, false, 8, 448);
+      } else {
+        SDPM_SWEEP4(false, false, false, 8, 448);
+      }
+    } else if (tx == 128) {
       if (box)
         SDPM_SWEEP4_W(true, 16, 768);
       else
@@ -2373,59 +2395,63 @@ void launch_sweeps4(const float* e, float* e_out, const float* r, int n, float s
     return;
   }
   if (!first && e != e_out)
-    hipMemcpyAsync(e_out, e, (size_t)n * n * n * sizeof(float), hipMemcpyDeviceToDevice, st);
+    hipMemcpyAsync(e_out, e, (size_t)n * n * n * sizeof(T), hipMemcpyDeviceToDevice, st);
   Level L{};
   L.n = n;
   L.box = b;
-  sweep_run<float>(e_out, r, L, 1, 0, 4, first, scale, inv_diag, st);
+  sweep_run<T>(e_out, r, L, 1, 0, 4, first, scale, inv_diag, st);
   if (t) {
     const int txv = v4_threads(b);
     const dim3 g = v4_grid(b, txv);
     if (txv == 64)
-      hipLaunchKernelGGL((k_resid_red_v4<float, 64>), g, dim3(64, 4), 0, st, e_out, r, t, n, b,
+      hipLaunchKernelGGL((k_resid_red_v4<T, 64>), g, dim3(64, 4), 0, st, e_out, r, t, n, b,
                          inv_scale, kappa);
     else if (txv == 32)
-      hipLaunchKernelGGL((k_resid_red_v4<float, 32>), g, dim3(32, 8), 0, st, e_out, r, t, n, b,
+      hipLaunchKernelGGL((k_resid_red_v4<T, 32>), g, dim3(32, 8), 0, st, e_out, r, t, n, b,
                          inv_scale, kappa);
     else
-      hipLaunchKernelGGL((k_resid_red_v4<float, 16>), g, dim3(16, 16), 0, st, e_out, r, t, n, b,
+      hipLaunchKernelGGL((k_resid_red_v4<T, 16>), g, dim3(16, 16), 0, st, e_out, r, t, n, b,
                          inv_scale, kappa);
   }
 }
 
-// The fused form of pre or post sweeps on level L when it applies (FP32,
-// nsweeps == 2 red-black pairs, a periodic level of at least kSweep4Min
-// cells a side with an e_alt array): from a zero guess it writes e, else it
-// reads e and writes e_alt, and the two swap.  False when it does not apply.
+template void launch_sweeps4<float>(const float*, float*, const float*, int, float, float, bool, bool,
+                                    float*, float, float, const Box*, hipStream_t);
+template void launch_sweeps4<double>(const double*, double*, const double*, int, double, double, bool,
+                                     bool, double*, double, double, const Box*, hipStream_t);
+
+// The fused form of pre or post sweeps on level L when it applies (nsweeps ==
+// 2 red-black pairs, a level of at least kSweep4Min cells a side): from a zero
+// guess it writes e, else it reads e and writes a second array, and the two
+// swap: e_alt, or on an FP64 level t, the residual's scratch, which is free
+// then (resid, the residual into t, is the FP32 form's alone) and like them
+// zero outside the box.  False when it does not apply.
 template <typename T>
 static bool sweeps4(Level& L, int level, bool periodic, int nsweeps, bool zero, T scale, T inv_diag,
                     hipStream_t st, bool resid = false, T inv_scale = 0, T kappa = 0) {
-  if constexpr (sizeof(T) != 4) {
+  const Box fb = whole_mesh(L.n);
+  bool whole = true;
+  for (int d = 0; d < 3; ++d) whole = whole && L.box.lo[d] == fb.lo[d] && L.box.hi[d] == fb.hi[d];
+  void*& alt = sizeof(T) == 4 ? L.e_alt : L.t;
+  // a frozen-exterior box (which keeps a plane from every face) with at
+  // least 128^3 cells; periodic levels are whole
+  if (nsweeps != 2 || L.n < kSweep4Min || !alt || (periodic && !whole) ||
+      (!periodic && box_cells(L.box) < (int64_t)1 << 21))
     return false;
-  } else {
-    const Box fb = whole_mesh(L.n);
-    bool whole = true;
-    for (int d = 0; d < 3; ++d) whole = whole && L.box.lo[d] == fb.lo[d] && L.box.hi[d] == fb.hi[d];
-    // a frozen-exterior box (which keeps a plane from every face) with at
-    // least 128^3 cells; periodic levels are whole
-    if (nsweeps != 2 || L.n < kSweep4Min || !L.e_alt || (periodic && !whole) ||
-        (!periodic && box_cells(L.box) < (int64_t)1 << 21))
-      return false;
-    // ids: coarser levels; the finest level's passes from the zero guess
-    // (with the residual), continuing with the residual (pre-smoothing of a
-    // further cycle) and without it (post-smoothing)
-    const int id = level > 0 ? K_SWEEP4_COARSE : zero ? K_SWEEP4_FIRST : resid ? K_SWEEP4_RESID : K_SWEEP4;
-    prof_begin(st, id);
-    float* out = zero ? (float*)L.e : (float*)L.e_alt;
-    launch_sweeps4((const float*)L.e, out, (const float*)L.r, L.n, scale, inv_diag, zero, true,
-                   resid ? (float*)L.t : nullptr, inv_scale, kappa, periodic ? nullptr : &L.box, st);
-    if (!zero) std::swap(L.e, L.e_alt);
-    // r read, e written (4 + 4 bytes per cell); without the zero guess the
-    // black half of e read too (2 more); with the residual the red half of t
-    // written instead of the red half of e (the same 2)
-    prof_end(st, id, (zero ? 8.0 : 10.0) * (double)box_cells(L.box));
-    return true;
-  }
+  // ids: coarser levels; the finest level's passes from the zero guess
+  // (with the residual), continuing with the residual (pre-smoothing of a
+  // further cycle) and without it (post-smoothing)
+  const int id = level > 0 ? K_SWEEP4_COARSE : zero ? K_SWEEP4_FIRST : resid ? K_SWEEP4_RESID : K_SWEEP4;
+  prof_begin(st, id);
+  launch_sweeps4<T>((const T*)L.e, zero ? (T*)L.e : (T*)alt, (const T*)L.r, L.n, scale, inv_diag, zero,
+                    true, resid && sizeof(T) == 4 ? (T*)L.t : nullptr, inv_scale, kappa,
+                    periodic ? nullptr : &L.box, st);
+  if (!zero) std::swap(L.e, alt);
+  // r read, e written (both whole); without the zero guess the black half of
+  // e read too; with the residual the red half of t written instead of the
+  // red half of e
+  prof_end(st, id, (zero ? 2.0 : 2.5) * sizeof(T) * (double)box_cells(L.box));
+  return true;
 }
 
 template <typename T>
@@ -2571,11 +2597,11 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
       prof_end(st, l == 0 ? K_SMOOTH : K_SMOOTH_COARSE, (zero ? 3 : 4) * 1.5 * es * cells, zero ? 3 : 4);
       continue;
     }
-    // the fused pre-smoothing forms the red residual itself
-    if (!sweeps4<T>(L, l, periodic, pre, zero, scale, inv_diag, st, true, inv_scale, (T)kappa)) {
-      sweep_run<T>((T*)L.e, r, L, l, 0, 2 * pre, zero, scale, inv_diag, st);
+    // the fused pre-smoothing of an FP32 level forms the red residual itself
+    const bool fused = sweeps4<T>(L, l, periodic, pre, zero, scale, inv_diag, st, true, inv_scale, (T)kappa);
+    if (!fused) sweep_run<T>((T*)L.e, r, L, l, 0, 2 * pre, zero, scale, inv_diag, st);
+    if (!fused || sizeof(T) == 8)
       resid_red<T>((const T*)L.e, r, (T*)L.t, L, inv_scale, (T)kappa, st);
-    }
     const Level& C = lv[l + 1];
     prof_begin(st, K_RESTRICT);
     restrict_level<T>(L, C, st);
