@@ -326,6 +326,17 @@ template <typename PT>
 void launch_block_deposit(const ParticleArgs& pa, double drift_coef, int drift, const MeshMap& mm,
                           const int64_t* block_start, uint64_t* counts, uint32_t* flags,
                           hipStream_t st);
+// The deposit of particles in any order (pk.hip): the order of the blocks of
+// kBlkCells^3 cells (sort.hip), perm[i] the i-th particle in it, and the CIC
+// deposit through it, for meshes of at least 4 blocks a side.  far_pairs adds
+// to count[0] the pairs (64 q, 64 q + 1) of particles further apart than a
+// block's side, as a measure of how far the order is from a spatial one.
+size_t block_order_bytes(int64_t n, int ng);
+void launch_block_order(const ParticleArgs& pa, int ng, double box, void* scratch,
+                        const uint32_t** perm, const int64_t** block_start, hipStream_t st);
+void launch_order_deposit(const ParticleArgs& pa, const MeshMap& mm, const int64_t* block_start,
+                          const uint32_t* perm, uint64_t* counts, uint32_t* flags, hipStream_t st);
+void launch_far_pairs(const ParticleArgs& pa, int ng, double box, uint32_t* count, hipStream_t st);
 
 // Learned warm start (net.hip).
 constexpr int kNetParams = 5 * (27 * 16 * 16 + 16);

@@ -902,10 +902,12 @@ __device__ inline uint32_t compact3(uint32_t v) {
   return v;
 }
 
-template <typename PT, bool DRIFT, int S>
+// PERM: sorted particle i is particle perm[i] of the arrays (no drift).
+template <typename PT, bool DRIFT, int S, bool PERM>
 __global__ void __launch_bounds__(1024)
 k_block_deposit(ParticleArgs pa, double coef, MeshMap mm, const int64_t* __restrict__ start,
-                unsigned long long* __restrict__ counts, uint32_t* __restrict__ flags) {
+                const uint32_t* __restrict__ perm, unsigned long long* __restrict__ counts,
+                uint32_t* __restrict__ flags) {
   constexpr int W = BlkWin<S>::W;
   __shared__ unsigned long long acc[W * W * W];
   const int64_t b = xcd_block();
@@ -921,9 +923,10 @@ k_block_deposit(ParticleArgs pa, double coef, MeshMap mm, const int64_t* __restr
   uint32_t bad_all = 0;
   for (int64_t i = s0 + threadIdx.x; i < s1; i += 1024) {
     double x[3];
+    const int64_t at = PERM ? (int64_t)perm[i] : i;
     for (int d = 0; d < 3; ++d) {
-      double v = __builtin_nontemporal_load(pa.x[d] + i);
-      if (DRIFT) v = drift_wrap(v, (double)__builtin_nontemporal_load((const PT*)pa.p[d] + i), coef, mm);
+      double v = PERM ? pa.x[d][at] : __builtin_nontemporal_load(pa.x[d] + at);
+      if (DRIFT) v = drift_wrap(v, (double)__builtin_nontemporal_load((const PT*)pa.p[d] + at), coef, mm);
       x[d] = v;
     }
     Frac c;
@@ -1025,8 +1028,8 @@ void launch_block_deposit(const ParticleArgs& pa, double drift_coef, int drift, 
   unsigned long long* cu = (unsigned long long*)counts;
   prof_begin(st, K_DEPOSIT);
 #define SDPM_BDEP(D, S)                                                                         \
-  hipLaunchKernelGGL((k_block_deposit<PT, D, S>), g, dim3(1024), 0, st, pa, drift_coef, mm,      \
-                     block_start, cu, flags)
+  hipLaunchKernelGGL((k_block_deposit<PT, D, S, false>), g, dim3(1024), 0, st, pa, drift_coef, mm, \
+                     block_start, nullptr, cu, flags)
   if (mm.tsc) {
     if (drift) SDPM_BDEP(true, 3); else SDPM_BDEP(false, 3);
   } else {
@@ -1037,6 +1040,17 @@ void launch_block_deposit(const ParticleArgs& pa, double drift_coef, int drift, 
   const double per = drift ? 24.0 + 3.0 * sizeof(PT) : 24.0;
   prof_end(st, K_DEPOSIT, per * pa.n + 8.0 * box_cells(mm.active));
 }
+void launch_order_deposit(const ParticleArgs& pa, const MeshMap& mm, const int64_t* block_start,
+                          const uint32_t* perm, uint64_t* counts, uint32_t* flags, hipStream_t st) {
+  if (pa.n <= 0) return;
+  const int64_t nb1 = mm.ng >> kBlkShift;
+  prof_begin(st, K_DEPOSIT);
+  hipLaunchKernelGGL((k_block_deposit<double, false, 2, true>), dim3((unsigned)(nb1 * nb1 * nb1)),
+                     dim3(1024), 0, st, pa, 0.0, mm, block_start, perm, (unsigned long long*)counts,
+                     flags);
+  prof_end(st, K_DEPOSIT, 28.0 * pa.n + 8.0 * box_cells(mm.active));
+}
+
 template void launch_block_deposit<float>(const ParticleArgs&, double, int, const MeshMap&,
                                           const int64_t*, uint64_t*, uint32_t*, hipStream_t);
 template void launch_block_deposit<double>(const ParticleArgs&, double, int, const MeshMap&,

@@ -221,7 +221,66 @@ void device_scan(uint32_t* a, int64_t n, uint32_t* part, hipStream_t st) {
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)np), dim3(256), 0, st, a, n, part);
 }
 
+// Sorts by key bits [from, to); the result is in k0, v0 (swapped on the way).
+void radix_sort(uint32_t*& k0, uint32_t*& v0, uint32_t*& k1, uint32_t*& v1, int64_t n, int from, int to,
+                uint32_t* hist, uint32_t* part, hipStream_t st) {
+  const int64_t nb = (n + kChunk - 1) / kChunk;
+  for (int bit = from; bit < to; bit += 8) {
+    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(256), 0, st, k0, n, bit, (int)nb, hist);
+    device_scan(hist, nb * kDigits, part, st);
+    hipLaunchKernelGGL((k_radix_scatter<true>), dim3((unsigned)nb), dim3(256), 0, st, k0, v0, n, bit,
+                       (int)nb, hist, k1, v1);
+    std::swap(k0, k1);
+    std::swap(v0, v1);
+  }
+}
+
+__global__ void __launch_bounds__(256)
+k_far_pairs(ParticleArgs pa, double inv_h, int ng, uint32_t* __restrict__ count) {
+  const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 64;
+  bool far = false;
+  if (q + 1 < pa.n)
+    for (int d = 0; d < 3; ++d) {
+      const double a = fabs(pa.x[d][q + 1] - pa.x[d][q]) * inv_h;
+      far = far || fmin(a, ng - a) > kBlkCells;
+    }
+  const uint32_t c = (uint32_t)__popcll(__ballot(far));
+  if ((threadIdx.x & 63) == 0 && c) atomicAdd(count, c);
+}
+
 }  // namespace
+
+void launch_far_pairs(const ParticleArgs& pa, int ng, double box, uint32_t* count, hipStream_t st) {
+  const int64_t pairs = (pa.n + 63) / 64;
+  hipLaunchKernelGGL(k_far_pairs, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, st, pa,
+                     (double)ng / box, ng, count);
+}
+
+size_t block_order_bytes(int64_t n, int ng) {
+  const int64_t nb1 = ng >> kBlkShift;
+  return sort_scratch_bytes(n) + (size_t)(nb1 * nb1 * nb1 + 1) * sizeof(int64_t);
+}
+
+void launch_block_order(const ParticleArgs& pa, int ng, double box, void* scratch,
+                        const uint32_t** perm, const int64_t** block_start, hipStream_t st) {
+  const int64_t n = pa.n, nb = (n + kChunk - 1) / kChunk, nb1 = ng >> kBlkShift, nblk = nb1 * nb1 * nb1;
+  int64_t* start = (int64_t*)scratch;
+  uint32_t* k0 = (uint32_t*)(start + nblk + 1);
+  uint32_t *v0 = k0 + n, *k1 = v0 + n, *v1 = k1 + n, *hist = v1 + n, *part = hist + nb * kDigits;
+  int lg = 0;
+  while ((1 << lg) < nb1) ++lg;
+  prof_begin(st, K_SORT);
+  hipLaunchKernelGGL(k_morton_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pa.x[0],
+                     pa.x[1], pa.x[2], n, (double)ng / box, ng, kBlkShift, k0, v0);
+  // the blocks alone: the order inside one is free
+  radix_sort(k0, v0, k1, v1, n, 2 * kBlkShift, 2 * kBlkShift + 3 * lg, hist, part, st);
+  hipLaunchKernelGGL(k_block_starts, dim3((unsigned)((nblk + 256) / 256)), dim3(256), 0, st, k0, n,
+                     kBlkShift, nblk, start);
+  const int passes = (3 * lg + 7) / 8;
+  prof_end(st, K_SORT, (double)n * (24.0 + 8.0 + passes * (4.0 + 16.0)));
+  *perm = v0;
+  *block_start = start;
+}
 
 size_t sort_scratch_bytes(int64_t capacity) {
   const int64_t nb = (capacity + kChunk - 1) / kChunk + 1;
@@ -250,14 +309,7 @@ void launch_morton_sort(const ParticleArgs& pa, int ng, double box, int shift, v
   prof_begin(st, K_SORT);
   hipLaunchKernelGGL(k_morton_keys, dim3(gp), dim3(256), 0, st, pa.x[0], pa.x[1], pa.x[2], n,
                      (double)ng / box, ng, shift, k0, v0);
-  for (int bit = 0; bit < bits; bit += 8) {
-    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(256), 0, st, k0, n, bit, (int)nb, hist);
-    device_scan(hist, tab, part, st);
-    hipLaunchKernelGGL((k_radix_scatter<true>), dim3((unsigned)nb), dim3(256), 0, st, k0, v0, n, bit,
-                       (int)nb, hist, k1, v1);
-    std::swap(k0, k1);
-    std::swap(v0, v1);
-  }
+  radix_sort(k0, v0, k1, v1, n, 0, bits, hist, part, st);
   if (block_start) {
     const int64_t nb1 = ng >> shift, nblk = nb1 * nb1 * nb1;
     hipLaunchKernelGGL(k_block_starts, dim3((unsigned)((nblk + 256) / 256)), dim3(256), 0, st, k0, n,
