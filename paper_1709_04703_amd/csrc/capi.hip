@@ -209,7 +209,7 @@ size_t carve(const sdpm_config& c, int64_t capacity, char* base, sdpm_ctx* ctx) 
     char* e = take(cells * el);
     char* r = take(cells * el);
     char* t = take(cells * el);
-    char* e_alt = el == 4 && n >= kSweep4Min ? take(cells * el) : nullptr;
+    char* e_alt = el == 4 && n >= kSweep4Alt ? take(cells * el) : nullptr;
     if (ctx) {
       ctx->lv[l].n = n;
       ctx->lv[l].e = e;

@@ -104,7 +104,7 @@ struct Level {
   void* r;    // right-hand side } red cells ((i+j+k) even) first, then black,
   void* t;    // residual        } each in row order with x index i >> 1
   void* e_alt;  // second correction array of the fused sweeps (FP32 levels of
-                // at least kSweep4Min cells a side; else null): they read one
+                // at least kSweep4Alt cells a side; else null): they read one
                 // and write the other, and the two swap
 };
 
@@ -217,7 +217,10 @@ void launch_tile_sweeps(const Level& L, int l, double kappa, bool periodic, int 
                         hipStream_t st);
 // Cells a side from which a level takes the fused four-sweep kernel (smaller
 // levels run too few workgroups for it).
-constexpr int kSweep4Min = 256;
+constexpr int kSweep4Min = 128;
+// Cells a side from which an FP32 level has an e_alt array, which the pass with
+// the residual in it needs (128^3: 22 us with it, 13.6 + 4.8 in two launches).
+constexpr int kSweep4Alt = 256;
 // Four colour sweeps (red, black, red, black) of a periodic level of n^3 cells, n a power of two >= 64: with fused, one k_sweep4 pass from e
 // (black colour; not read when first) into e_out (e_out == e allowed only
 // when first); otherwise e copied to e_out (not when first) and four

@@ -1167,12 +1167,14 @@ k_sweep4(const T* __restrict__ ein, T* __restrict__ eout, const T* __restrict__ 
     }
     __syncthreads();
   };
-  // whole groups of 6 steps (steps past ze only load)
+  // groups of 6 steps, the last one without RES of 4 or 6 (steps past ze only load)
   for (int z = zs; z <= ze; z += L) {
     step(z, StepPhase<0>{});
     step(z + 1, StepPhase<1>{});
     step(z + 2, StepPhase<2>{});
     step(z + 3, StepPhase<3>{});
+    // (with the residual the way out makes every step slower: 512^3 369 -> 417 us)
+    if (!RES && z + 4 > ze) break;
     step(z + 4, StepPhase<4>{});
     step(z + 5, StepPhase<5>{});
   }
@@ -2321,10 +2323,13 @@ static void sweep_run(T* e, const T* r, const Level& L, int level, int c0, int n
 // Planes per workgroup of the fused sweeps over `cols` columns and nz
 // planes: about one workgroup per compute unit (256; each chunk recomputes
 // 6 warm-up planes), at least 16 planes (512^3: 128 planes, 0.31 ms against
-// 0.33 ms with 64; 256^3: 16 planes, 48 us against 65 us with 32).
-static int sweep4_chunk(int cols, int nz) {
+// 0.33 ms with 64; 256^3: 16 planes, 48 us against 65 us with 32), 4 on a
+// smaller mesh, where nothing else fills the chip (128^3: 13.6 us a pass in FP32
+// and 22.6 in FP64, 8 planes 17.5 and 30.4; the four separate sweeps take 16.8
+// and 29.6 and three more gaps between launches).
+static int sweep4_chunk(int n, int cols, int nz) {
   const int per = std::max(1, cols * nz / 256);
-  int zc = 16;
+  int zc = n >= 256 ? 16 : 4;
   while (zc < nz && zc < per) zc <<= 1;
   return zc;
 }
@@ -2338,19 +2343,19 @@ void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag
   if (fused) {
     // 128 x 32-cell columns (one 768-thread workgroup per compute unit: 138
     // KB of LDS, 160 KB with the residual); 64 x 32 on a 64^3 mesh
-    // 128-cell columns on periodic levels of 128^3 and up and on boxes in
+    // 128-cell columns on periodic levels of 256^3 and up and on boxes in
     // meshes of 512^3 and up; 64-cell columns (two workgroups per CU) on
     // smaller meshes and on the boxes of the 256^3 level, where the chunks
     // of 128-cell columns are short (shrinking phase at 512^3:
     // 11.5 against 11.7 ms per step; on the periodic 256^3 level the wide
     // columns win, 0.72 against 0.86 ms per step)
-    const int tx = sizeof(T) == 4 && ((n >= 128 && !box) || n >= 512) ? 128 : 64;
+    const int tx = sizeof(T) == 4 && ((n >= 256 && !box) || n >= 512) ? 128 : 64;
     const int ux = tx / 8;
     const int hb = box ? ((b.lo[0] >> 1) & ~3) : 0;
     const int gx = box ? ((b.hi[0] >> 1) - hb + 4 * ux) / (4 * ux) : n / tx;
     const int gy = box ? (b.hi[1] - b.lo[1] + 32) / 32 : n / 32;
     const int nz = b.hi[2] - b.lo[2] + 1;
-    const int zc = sweep4_chunk(gx * gy, nz);
+    const int zc = sweep4_chunk(n, gx * gy, nz);
     const dim3 g((unsigned)(gx * gy * ((nz + zc - 1) / zc)));
 #define SDPM_SWEEP4(F, RS, BX, UXX, NTT)                                                              \
   hipLaunchKernelGGL((k_sweep4<T, F, RS, BX, UXX, 32, NTT>), g, dim3(NTT), 0, st, e, e_out, r, n, zc,    \
@@ -2423,35 +2428,36 @@ template void launch_sweeps4<double>(const double*, double*, const double*, int,
 // The fused form of pre or post sweeps on level L when it applies (nsweeps ==
 // 2 red-black pairs, a level of at least kSweep4Min cells a side): from a zero
 // guess it writes e, else it reads e and writes a second array, and the two
-// swap: e_alt, or on an FP64 level t, the residual's scratch, which is free
-// then (resid, the residual into t, is the FP32 form's alone) and like them
-// zero outside the box.  False when it does not apply.
+// swap: e_alt, or where the level has none t, the residual's scratch, which is
+// free then and like them zero outside the box.  Says what it did: kDone with
+// the red residual in t (on request, with an e_alt), kSwept without.
+enum Sweeps4 { kNotFused, kSwept, kDone };
 template <typename T>
-static bool sweeps4(Level& L, int level, bool periodic, int nsweeps, bool zero, T scale, T inv_diag,
-                    hipStream_t st, bool resid = false, T inv_scale = 0, T kappa = 0) {
+static Sweeps4 sweeps4(Level& L, int level, bool periodic, int nsweeps, bool zero, T scale, T inv_diag,
+                       hipStream_t st, bool resid = false, T inv_scale = 0, T kappa = 0) {
   const Box fb = whole_mesh(L.n);
   bool whole = true;
   for (int d = 0; d < 3; ++d) whole = whole && L.box.lo[d] == fb.lo[d] && L.box.hi[d] == fb.hi[d];
-  void*& alt = sizeof(T) == 4 ? L.e_alt : L.t;
+  void*& alt = L.e_alt ? L.e_alt : L.t;
+  resid = resid && L.e_alt;
   // a frozen-exterior box (which keeps a plane from every face) with at
   // least 128^3 cells; periodic levels are whole
-  if (nsweeps != 2 || L.n < kSweep4Min || !alt || (periodic && !whole) ||
+  if (nsweeps != 2 || L.n < kSweep4Min || (periodic && !whole) ||
       (!periodic && box_cells(L.box) < (int64_t)1 << 21))
-    return false;
+    return kNotFused;
   // ids: coarser levels; the finest level's passes from the zero guess
   // (with the residual), continuing with the residual (pre-smoothing of a
   // further cycle) and without it (post-smoothing)
   const int id = level > 0 ? K_SWEEP4_COARSE : zero ? K_SWEEP4_FIRST : resid ? K_SWEEP4_RESID : K_SWEEP4;
   prof_begin(st, id);
   launch_sweeps4<T>((const T*)L.e, zero ? (T*)L.e : (T*)alt, (const T*)L.r, L.n, scale, inv_diag, zero,
-                    true, resid && sizeof(T) == 4 ? (T*)L.t : nullptr, inv_scale, kappa,
-                    periodic ? nullptr : &L.box, st);
+                    true, resid ? (T*)L.t : nullptr, inv_scale, kappa, periodic ? nullptr : &L.box, st);
   if (!zero) std::swap(L.e, alt);
   // r read, e written (both whole); without the zero guess the black half of
   // e read too; with the residual the red half of t written instead of the
   // red half of e
   prof_end(st, id, (zero ? 2.0 : 2.5) * sizeof(T) * (double)box_cells(L.box));
-  return true;
+  return resid ? kDone : kSwept;
 }
 
 template <typename T>
@@ -2597,11 +2603,10 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
       prof_end(st, l == 0 ? K_SMOOTH : K_SMOOTH_COARSE, (zero ? 3 : 4) * 1.5 * es * cells, zero ? 3 : 4);
       continue;
     }
-    // the fused pre-smoothing of an FP32 level forms the red residual itself
-    const bool fused = sweeps4<T>(L, l, periodic, pre, zero, scale, inv_diag, st, true, inv_scale, (T)kappa);
-    if (!fused) sweep_run<T>((T*)L.e, r, L, l, 0, 2 * pre, zero, scale, inv_diag, st);
-    if (!fused || sizeof(T) == 8)
-      resid_red<T>((const T*)L.e, r, (T*)L.t, L, inv_scale, (T)kappa, st);
+    const Sweeps4 fused =
+        sweeps4<T>(L, l, periodic, pre, zero, scale, inv_diag, st, true, inv_scale, (T)kappa);
+    if (fused == kNotFused) sweep_run<T>((T*)L.e, r, L, l, 0, 2 * pre, zero, scale, inv_diag, st);
+    if (fused != kDone) resid_red<T>((const T*)L.e, r, (T*)L.t, L, inv_scale, (T)kappa, st);
     const Level& C = lv[l + 1];
     prof_begin(st, K_RESTRICT);
     restrict_level<T>(L, C, st);
@@ -2658,7 +2663,7 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
     prof_begin(st, K_PROLONG);
     prolong_level<T>(L, C, post == 0, st);
     prof_end(st, K_PROLONG, es * ((post > 0 ? 1.0 : 2.0) * cells + (double)box_cells(C.box)));
-    if (!sweeps4<T>(L, l, periodic, post, false, scale, inv_diag, st))
+    if (sweeps4<T>(L, l, periodic, post, false, scale, inv_diag, st) == kNotFused)
       sweep_run<T>((T*)L.e, (const T*)L.r, L, l, 0, 2 * post, false, scale, inv_diag, st);
   }
   return (const T*)lv[0].e;
