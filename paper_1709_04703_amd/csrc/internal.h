@@ -234,7 +234,8 @@ constexpr int kSweep4Alt = 256;
 // mesh, e being zero outside it.
 template <typename T>
 void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag, bool first,
-                    bool fused, T* t, T inv_scale, T kappa, const Box* box, hipStream_t st);
+                    bool fused, T* t, T inv_scale, T kappa, const Box* box, hipStream_t st,
+                    const T* coarse = nullptr);
 
 // ---------------------------------------------------------------------------
 // Launchers, particle kernels (particles.hip).

@@ -927,6 +927,12 @@ k_smooth_color_v4(T* __restrict__ eo, const T* __restrict__ ex, const T* __restr
 // from zero, against 172 and 154 in separate sweeps (which move 48 bytes a cell
 // at the rate of a copy); FP64 step on 256^3 with TSC 5.53 -> 4.51 ms.
 //
+// PROL (post-smoothing): the input black values are corrected by the next
+// level's prolonged correction on the way in, which saves the pass that reads
+// and writes them for it: 512^3 423 -> 334 us for both, 256^3 61 -> 52, 128^3
+// 19.2 -> 16.7 (with the loads of the coarse rows in every step, not every
+// other: 386, 61 and 19.7).
+//
 // Requires n a power of two >= 8 UX, n % zc == 0.  FIRST: the red sweep starts
 // from e = 0 and ein is not read (eout may be the level's e); otherwise ein
 // supplies the black colour and must not alias eout (other workgroups still
@@ -936,11 +942,11 @@ struct StepPhase {
   static constexpr int value = V;
 };
 
-template <typename T, bool FIRST, bool RES, bool BOX, int UX, int TY, int NT>
+template <typename T, bool FIRST, bool RES, bool PROL, bool BOX, int UX, int TY, int NT>
 __global__ void __launch_bounds__(NT)
 k_sweep4(const T* __restrict__ ein, T* __restrict__ eout, const T* __restrict__ r, int n,
          int zc, T scale, T inv_diag, T* __restrict__ tout, T inv_scale, T kappa,
-         Box b) {
+         Box b, const T* __restrict__ coarse) {
   constexpr int G = RES ? 1 : 0;                 // the residual: one more stage
   constexpr int HY = 4 + G;                      // halo rows per side
   constexpr int U = UX + 2, HW = 4 * U, RY = TY + 2 * HY, PL = RY * HW;   // region: U units x RY rows
@@ -958,7 +964,7 @@ k_sweep4(const T* __restrict__ ein, T* __restrict__ eout, const T* __restrict__ 
   const Tile tl = BOX ? tile_of(((b.hi[0] >> 1) - hb + 4 * UX) / (4 * UX), (b.hi[1] - b.lo[1] + TY) / TY)
                       : tile_of(n / (8 * UX), n / TY);
   const int H0 = hb + tl.bx * 4 * UX, Y0 = (BOX ? b.lo[1] : 0) + tl.by * TY;
-  const int Z0 = (BOX ? b.lo[2] : 0) + tl.bz * zc;
+  const int Z0 = (BOX ? b.lo[2] & ~(PROL ? 1 : 0) : 0) + tl.bz * zc;
   const int zend = BOX ? min(Z0 + zc, b.hi[2] + 1) : Z0 + zc;   // output planes [Z0, zend)
   const int tid = threadIdx.x;
   const bool ok = tid < ITEMS;
@@ -1015,6 +1021,46 @@ k_sweep4(const T* __restrict__ ein, T* __restrict__ eout, const T* __restrict__ 
   const int zs = Z0 - 3 - G, ze = Z0 + zc + 2 + G;
   auto ld_r = [&](int c, int z) { return *(const Vec4<T>*)(r + c * oth + (int64_t)(z & m) * pls + jh); };
   auto ld_e = [&](int z) { return *(const Vec4<T>*)(ein + oth + (int64_t)(z & m) * pls + jh); };
+  // PROL: the black values of e are corrected by the prolonged coarse cells as
+  // they are staged, in the order of k_prolong_black_v4.  A unit draws on cells
+  // X0 .. X0 + 4, X0 its half index, of the rows J of the coarse plane z / 2
+  // and, for odd z, of the next: csum holds their sum over the rows of the one
+  // plane, cq the rows of the other, loaded every other step ahead of use (Z0
+  // is even, so the step knows the parity)
+  const int nc = hn, mc = nc - 1, X0 = (H0 - 4 + 4 * u) & hm;
+  const int J[2] = {jj >> 1, ((jj + 1) >> 1) & mc};
+  const bool dy = jj & 1;
+  T csum[PROL ? 5 : 1], cq[2][PROL ? 5 : 1];
+  auto ld_c = [&](int z) {                       // rows of plane (z + 1) / 2
+    const int K = (((z & m) + 1) >> 1) & mc;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int c0 = (J[q] + K) & 1;
+      const int64_t row = ((int64_t)K * nc + J[q]) * (nc >> 1), hc = (int64_t)nc * nc * (nc >> 1);
+      const Vec2<T> a = *(const Vec2<T>*)(coarse + c0 * hc + row + (X0 >> 1));
+      const Vec2<T> bb = *(const Vec2<T>*)(coarse + (c0 ^ 1) * hc + row + (X0 >> 1));
+      cq[q][0] = a.v[0], cq[q][1] = bb.v[0], cq[q][2] = a.v[1], cq[q][3] = bb.v[1];
+      cq[q][4] = coarse[c0 * hc + row + (((X0 + 4) & mc) >> 1)];
+    }
+  };
+  auto sum_c = [&]() {
+#pragma unroll
+    for (int x = 0; x < 5; ++x) csum[x] = cq[0][x] + (dy ? cq[1][x] : (T)0);
+  };
+  auto prolong = [&](int z, auto odd, Vec4<T>& v) {
+    constexpr bool dz = decltype(odd)::value;
+    const int p = (1 + jj + dz) & 1;
+    T l[5];
+#pragma unroll
+    for (int x = 0; x < 5; ++x) {
+      l[x] = csum[x];
+      if (dz) l[x] = (l[x] + cq[0][x]) + (dy ? cq[1][x] : (T)0);
+    }
+    if (dz) sum_c();
+    const T w = (T)(dz ? 0.125 : 0.25) * (T)(dy ? 1 : 2);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) v.v[x] = v.v[x] + w * (l[x] + (p ? l[x + 1] : l[x]));
+  };
   auto ld_x = [&](int z) { return ein[oth + (int64_t)(z & m) * pls + jx]; };
   // colour c on plane z, rows [lo, RY - lo): s* = the other colour's planes
   // z - 1, z, z + 1; the result goes to ov and (keep) to dst
@@ -1089,7 +1135,23 @@ k_sweep4(const T* __restrict__ ein, T* __restrict__ eout, const T* __restrict__ 
   // zs - 2 .. zs + D - 1, black r planes zs - 3 .. zs + D - 2, black e
   // planes zs + 2 .. zs + L + 1 (all in bounds: plane indices wrap)
   if (!FIRST) {
-    for (int z = zs - 1; z <= zs + 1; ++z) stage_black(z, ld_e(z), RES ? ld_x(z) : (T)0);
+    if constexpr (PROL) {
+      ld_c(zs - 1);
+      sum_c();
+    }
+    for (int z = zs - 1; z <= zs + 1; ++z) {
+      Vec4<T> v = ld_e(z);
+      if constexpr (PROL) {
+        if (z == zs) {
+          ld_c(z);
+          prolong(z, StepPhase<1>{}, v);
+        } else {
+          prolong(z, StepPhase<0>{}, v);
+        }
+      }
+      stage_black(z, v, RES ? ld_x(z) : (T)0);
+    }
+    if constexpr (PROL) ld_c(zs + 2);
   }
 #pragma unroll
   for (int x = -2; x < D; ++x) qr[(x + L) % L] = ld_r(0, zs + x);
@@ -1127,9 +1189,11 @@ k_sweep4(const T* __restrict__ ein, T* __restrict__ eout, const T* __restrict__ 
       if constexpr (RES) holdx = qx[(P + 2) % L];
       if (!RES && ok && z <= ze) {
         Vec4<T> v = hold;
+        if constexpr (PROL) prolong(z + 2, StepPhase<(P + 1) & 1>{}, v);
         mask(1, z + 2, hu, v);
         *(Vec4<T>*)(B(P2{}) + base) = v;
       }
+      if constexpr (PROL && (P & 1) == 0) ld_c(z + 4);
       qe[(P + 2) % L] = ld_e(z + 2 + L);
       if constexpr (RES) qx[(P + 2) % L] = ld_x(z + 2 + L);
     }
@@ -2338,7 +2402,8 @@ static Box whole_mesh(int n) { return Box{{0, 0, 0}, {n - 1, n - 1, n - 1}}; }
 
 template <typename T>
 void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag, bool first,
-                    bool fused, T* t, T inv_scale, T kappa, const Box* box, hipStream_t st) {
+                    bool fused, T* t, T inv_scale, T kappa, const Box* box, hipStream_t st,
+                    const T* coarse) {
   const Box b = box ? *box : whole_mesh(n);
   if (fused) {
     // 128 x 32-cell columns (one 768-thread workgroup per compute unit: 138
@@ -2354,12 +2419,13 @@ void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag
     const int hb = box ? ((b.lo[0] >> 1) & ~3) : 0;
     const int gx = box ? ((b.hi[0] >> 1) - hb + 4 * ux) / (4 * ux) : n / tx;
     const int gy = box ? (b.hi[1] - b.lo[1] + 32) / 32 : n / 32;
-    const int nz = b.hi[2] - b.lo[2] + 1;
+    const int nz = b.hi[2] - (coarse ? b.lo[2] & ~1 : b.lo[2]) + 1;
     const int zc = sweep4_chunk(n, gx * gy, nz);
     const dim3 g((unsigned)(gx * gy * ((nz + zc - 1) / zc)));
-#define SDPM_SWEEP4(F, RS, BX, UXX, NTT)                                                              \
-  hipLaunchKernelGGL((k_sweep4<T, F, RS, BX, UXX, 32, NTT>), g, dim3(NTT), 0, st, e, e_out, r, n, zc,    \
-                     scale, inv_diag, t, inv_scale, kappa, b)
+#define SDPM_SWEEP4P(F, RS, PR, BX, UXX, NTT)                                                       \
+  hipLaunchKernelGGL((k_sweep4<T, F, RS, PR, BX, UXX, 32, NTT>), g, dim3(NTT), 0, st, e, e_out, r, n,  \
+                     zc, scale, inv_diag, t, inv_scale, kappa, b, coarse)
+#define SDPM_SWEEP4(F, RS, BX, UXX, NTT) SDPM_SWEEP4P(F, RS, false, BX, UXX, NTT)
 #define SDPM_SWEEP4_W(BX, UXX, NTT)               \
   do {                                            \
     if (first && t)                               \
@@ -2368,6 +2434,8 @@ void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag
       SDPM_SWEEP4(true, false, BX, UXX, NTT);     \
     else if (t)                                   \
       SDPM_SWEEP4(false, true, BX, UXX, NTT);     \
+    else if (coarse)                              \
+      SDPM_SWEEP4P(false, false, true, BX, UXX, NTT); \
     else                                          \
       SDPM_SWEEP4(false, false, BX, UXX, NTT);    \
   } while (0)
@@ -2377,10 +2445,14 @@ void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag
       if (box) {
         if (first)
           SDPM_SWEEP4(true, false, true, 8, 448);
+        else if (coarse)
+          SDPM_SWEEP4P(false, false, true, true, 8, 448);
         else
           SDPM_SWEEP4(false, false, true, 8, 448);
       } else if (first) {
         SDPM_SWEEP4(true, false, false, 8, 448);
+      } else if (coarse) {
+        SDPM_SWEEP4P(false, false, true, false, 8, 448);
       } else {
         SDPM_SWEEP4(false, false, false, 8, 448);
       }
@@ -2397,6 +2469,7 @@ void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag
     }
 #undef SDPM_SWEEP4_W
 #undef SDPM_SWEEP4
+#undef SDPM_SWEEP4P
     return;
   }
   if (!first && e != e_out)
@@ -2421,9 +2494,10 @@ void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag
 }
 
 template void launch_sweeps4<float>(const float*, float*, const float*, int, float, float, bool, bool,
-                                    float*, float, float, const Box*, hipStream_t);
+                                    float*, float, float, const Box*, hipStream_t, const float*);
 template void launch_sweeps4<double>(const double*, double*, const double*, int, double, double, bool,
-                                     bool, double*, double, double, const Box*, hipStream_t);
+                                     bool, double*, double, double, const Box*, hipStream_t,
+                                     const double*);
 
 // The fused form of pre or post sweeps on level L when it applies (nsweeps ==
 // 2 red-black pairs, a level of at least kSweep4Min cells a side): from a zero
@@ -2434,7 +2508,8 @@ template void launch_sweeps4<double>(const double*, double*, const double*, int,
 enum Sweeps4 { kNotFused, kSwept, kDone };
 template <typename T>
 static Sweeps4 sweeps4(Level& L, int level, bool periodic, int nsweeps, bool zero, T scale, T inv_diag,
-                       hipStream_t st, bool resid = false, T inv_scale = 0, T kappa = 0) {
+                       hipStream_t st, bool resid = false, T inv_scale = 0, T kappa = 0,
+                       const T* coarse = nullptr) {
   const Box fb = whole_mesh(L.n);
   bool whole = true;
   for (int d = 0; d < 3; ++d) whole = whole && L.box.lo[d] == fb.lo[d] && L.box.hi[d] == fb.hi[d];
@@ -2451,12 +2526,12 @@ static Sweeps4 sweeps4(Level& L, int level, bool periodic, int nsweeps, bool zer
   const int id = level > 0 ? K_SWEEP4_COARSE : zero ? K_SWEEP4_FIRST : resid ? K_SWEEP4_RESID : K_SWEEP4;
   prof_begin(st, id);
   launch_sweeps4<T>((const T*)L.e, zero ? (T*)L.e : (T*)alt, (const T*)L.r, L.n, scale, inv_diag, zero,
-                    true, resid ? (T*)L.t : nullptr, inv_scale, kappa, periodic ? nullptr : &L.box, st);
+                    true, resid ? (T*)L.t : nullptr, inv_scale, kappa, periodic ? nullptr : &L.box, st, coarse);
   if (!zero) std::swap(L.e, alt);
   // r read, e written (both whole); without the zero guess the black half of
   // e read too; with the residual the red half of t written instead of the
   // red half of e
-  prof_end(st, id, (zero ? 2.0 : 2.5) * sizeof(T) * (double)box_cells(L.box));
+  prof_end(st, id, ((zero ? 2.0 : 2.5) + (coarse ? 0.125 : 0.0)) * sizeof(T) * (double)box_cells(L.box));
   return resid ? kDone : kSwept;
 }
 
@@ -2660,11 +2735,14 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
       prof_end(st, l == 0 ? K_SMOOTH : K_SMOOTH_COARSE, 4 * 1.5 * es * cells, 4);
       continue;
     }
+    // the fused post-smoothing prolongs the correction itself
+    if (sweeps4<T>(L, l, periodic, post, false, scale, inv_diag, st, false, (T)0, (T)0,
+                   (const T*)C.e) != kNotFused)
+      continue;
     prof_begin(st, K_PROLONG);
     prolong_level<T>(L, C, post == 0, st);
     prof_end(st, K_PROLONG, es * ((post > 0 ? 1.0 : 2.0) * cells + (double)box_cells(C.box)));
-    if (sweeps4<T>(L, l, periodic, post, false, scale, inv_diag, st) == kNotFused)
-      sweep_run<T>((T*)L.e, (const T*)L.r, L, l, 0, 2 * post, false, scale, inv_diag, st);
+    sweep_run<T>((T*)L.e, (const T*)L.r, L, l, 0, 2 * post, false, scale, inv_diag, st);
   }
   return (const T*)lv[0].e;
 }

@@ -1,6 +1,7 @@
-"""FP64 solves on a mesh whose finest level takes the fused four-sweep pass:
-periodic, and frozen-exterior boxes whose faces lie inside a column's units
-and rows, from zero and from the correction of the cycle before.  The result
+"""Solves on a mesh whose finest levels take the fused four-sweep passes, the
+last with the coarser level's correction prolonged in it: periodic, and
+frozen-exterior boxes whose faces lie inside a column's units and rows and on
+planes of either parity, from zero and from the correction of the cycle before.  The result
 is checked by its residual, evaluated in NumPy, and every V(2,2) cycle has to
 cut the residual as the separate sweeps do."""
 from __future__ import annotations
@@ -21,10 +22,11 @@ def _relative_residual(phi, rhs, kappa, sl):
     return np.linalg.norm(r) / np.linalg.norm(rhs[sl])
 
 
-@pytest.mark.parametrize("radius", [None, 65.5, 90.2])
+@pytest.mark.parametrize("radius", [None, 64.6, 65.5, 90.2])
+@pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("kappa", [0.0, 0.09])
 @pytest.mark.parametrize("per_outer", [1, 3])
-def test_solve_256(radius, kappa, per_outer):
+def test_solve_256(radius, prec, kappa, per_outer):
     import torch
 
     ng, box, n, tol = 256, 2560.0, 40000, 1e-9
@@ -32,7 +34,7 @@ def test_solve_256(radius, kappa, per_outer):
     # (kappa = 0 on boxes that the coarser meshes cannot hold does not converge,
     # whatever kernel sweeps them: aligned boxes there)
     align = dict(box_align=1) if kappa else {}
-    cfg = lib_config(ng, box, precision=1, tol=tol, n_initial=n, shrink=0 if radius is None else 1,
+    cfg = lib_config(ng, box, precision=prec, tol=tol, n_initial=n, shrink=0 if radius is None else 1,
                      cycles_per_outer=per_outer, **align)
     sim = make_sim(cfg, n)
     sim.bind(x, p, ids)
