@@ -1298,36 +1298,6 @@ k_resid_red_v4(const T* __restrict__ e, const T* __restrict__ r, T* __restrict__
   }
 }
 
-// t = r - A_l e on the red cells of the box.  After a sweep that ends with
-// the black colour the black residual is zero (each black equation was just
-// solved exactly), so t keeps zeros there (t is cleared with the levels).
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_resid_red(const T* __restrict__ e, const T* __restrict__ r, T* __restrict__ tout, int n, Box b,
-            T inv_scale, T kappa) {
-  const Tile tl = tile_half(b);
-  const int j = b.lo[1] + tl.by * kBoxTy + threadIdx.y;
-  if (j > b.hi[1]) return;
-  const int h = (b.lo[0] >> 1) + tl.bx * kBoxTx + threadIdx.x;
-  const int m = n - 1, hn = n >> 1;
-  const int64_t oth = half_cells(n);
-  const int k0 = b.lo[2] + tl.bz * kBoxKz;
-  const int k1 = min(k0 + kBoxKz - 1, b.hi[2]);
-  const int jp = (j + 1) & m, jm = (j - 1) & m;
-  for (int k = k0; k <= k1; ++k) {
-    const int i = 2 * h + ((j + k) & 1);
-    if (i < b.lo[0] || i > b.hi[0]) continue;
-    const int kp = (k + 1) & m, km = (k - 1) & m;
-    const int64_t row = ((int64_t)k * n + j) * hn;
-    const int64_t c = row + h;
-    const T ctr = e[c];
-    const T nb = e[oth + row + (((i - 1) & m) >> 1)] + e[oth + row + (((i + 1) & m) >> 1)] +
-                 e[oth + ((int64_t)k * n + jm) * hn + h] + e[oth + ((int64_t)k * n + jp) * hn + h] +
-                 e[oth + ((int64_t)km * n + j) * hn + h] + e[oth + ((int64_t)kp * n + j) * hn + h];
-    tout[c] = r[c] - (nb - (T)6 * ctr) * inv_scale + kappa * ctr;
-  }
-}
-
 // Full weighting: r_c(I) = sum_{o in {-1,0,1}^3} w(o) t_f(2I + o),
 // w = (1/4, 1/2, 1/4) per axis.  Only red fine cells (o_x + o_y + o_z even)
 // carry a residual.
@@ -1400,6 +1370,96 @@ k_prolong(const T* __restrict__ ec, T* __restrict__ ef, int nc, int nf, Box bf, 
                   cs[z1][y0][x0] + cs[z1][y0][x1] + cs[z1][y1][x0] + cs[z1][y1][x1];
       ef[color * hc + row] += (T)0.125 * a;
     }
+  }
+}
+
+// The residual r - A_l e of a level restricted onto the next.  After a sweep
+// that ends with the black colour the black residual is zero (each black
+// equation was just solved exactly), so only the red cells of k_restrict's
+// stencil count.  A workgroup takes kRrX x kRrY x CZ coarse cells: the red
+// residuals under them (and one cell around, computed by the neighbours too)
+// go to LDS and are weighted there, so that the residual neither goes to memory
+// nor comes back.  Same arithmetic as a residual in memory and its restriction;
+// V4: in the order of k_restrict_v4.
+// Bound by the loads, eight a residual, from the caches: 256^3 in FP64 67 us
+// with CZ = 8 (59 + 21 in two launches; 73 with CZ = 4); 128^3, where a
+// workgroup's own chain of loads counts, with CZ = 2 11.0 us (10.4 + 6.5; 12.2
+// with CZ = 8), in FP32 8.0 (4.9 + 3.6 and a gap; 10.7).
+constexpr int kRrX = 32, kRrY = 4;
+
+template <typename T, bool V4, int CZ>
+__global__ void __launch_bounds__(256)
+k_resid_restrict(const T* __restrict__ e, const T* __restrict__ r, T* __restrict__ rc, int n, int nc,
+                 Box b, Box bc, T inv_scale, T kappa) {
+  constexpr int RH = kRrX + 1, RY = 2 * kRrY + 1, RZ = 2 * CZ + 1, NQ = RH * RY * RZ;
+  constexpr int kRrG = CZ == 8 ? 4 : 6;          // residuals whose loads go out together
+  __shared__ T t[NQ];
+  const Tile tl = tile_of((bc.hi[0] - bc.lo[0] + kRrX) / kRrX, (bc.hi[1] - bc.lo[1] + kRrY) / kRrY);
+  const int I0 = bc.lo[0] + tl.bx * kRrX, J0 = bc.lo[1] + tl.by * kRrY, K0 = bc.lo[2] + tl.bz * CZ;
+  const int m = n - 1, hn = n >> 1;
+  const int64_t oth = half_cells(n);
+  // a periodic axis wraps: its box spans it
+  bool wrap[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) wrap[d] = b.lo[d] == 0 && b.hi[d] == m;
+  // cells outside the box read some cell of the mesh and count as 0; the last
+  // threads repeat the last cell
+  for (int u = 0; u < (NQ + 255) / 256; u += kRrG) {
+    T ld[kRrG][8];
+    bool in[kRrG];
+#pragma unroll
+    for (int g = 0; g < kRrG; ++g) {
+      const unsigned q = min(threadIdx.x + 256u * (u + g), NQ - 1u);
+      const int h = q % RH, y = q / RH % RY, z = q / (RH * RY);
+      const int j = 2 * J0 - 1 + y, k = 2 * K0 - 1 + z, i = 2 * I0 + 2 * h - ((j + k) & 1);
+      in[g] = (wrap[0] || (i >= b.lo[0] && i <= b.hi[0])) &&
+              (wrap[1] || (j >= b.lo[1] && j <= b.hi[1])) &&
+              (wrap[2] || (k >= b.lo[2] && k <= b.hi[2]));
+      const int jw = j & m, kw = k & m, hw = (i & m) >> 1;
+      const int64_t row = ((int64_t)kw * n + jw) * hn;
+      ld[g][0] = e[oth + row + (((i - 1) & m) >> 1)];
+      ld[g][1] = e[oth + row + (((i + 1) & m) >> 1)];
+      ld[g][2] = e[oth + ((int64_t)kw * n + ((j - 1) & m)) * hn + hw];
+      ld[g][3] = e[oth + ((int64_t)kw * n + ((j + 1) & m)) * hn + hw];
+      ld[g][4] = e[oth + ((int64_t)((k - 1) & m) * n + jw) * hn + hw];
+      ld[g][5] = e[oth + ((int64_t)((k + 1) & m) * n + jw) * hn + hw];
+      ld[g][6] = e[row + hw];
+      ld[g][7] = r[row + hw];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < kRrG; ++g) {
+      const T nb = ld[g][0] + ld[g][1] + ld[g][2] + ld[g][3] + ld[g][4] + ld[g][5], ctr = ld[g][6];
+      const T v = ld[g][7] - (nb - (T)6 * ctr) * inv_scale + kappa * ctr;
+      t[min(threadIdx.x + 256u * (u + g), NQ - 1u)] = in[g] ? v : (T)0;
+    }
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < kRrX * kRrY * CZ; q += 256) {
+    const int x = q % kRrX, y = q / kRrX % kRrY, z = q / (kRrX * kRrY);
+    const int I = I0 + x, J = J0 + y, K = K0 + z;
+    if (I > bc.hi[0] || J > bc.hi[1] || K > bc.hi[2]) continue;
+    auto R = [&](int di, int dj, int dk) -> T {
+      return t[((2 * z + 1 + dk) * RY + 2 * y + 1 + dj) * RH + x + (di > 0 ? 1 : 0)];
+    };
+    const T centre = R(0, 0, 0);
+    T edges;
+    if constexpr (V4) {
+      edges = 0;
+      edges += R(-1, -1, 0) + R(1, -1, 0);
+      edges += R(-1, 1, 0) + R(1, 1, 0);
+      edges += R(-1, 0, -1) + R(1, 0, -1);
+      edges += R(-1, 0, 1) + R(1, 0, 1);
+      edges += R(0, -1, -1);
+      edges += R(0, 1, -1);
+      edges += R(0, -1, 1);
+      edges += R(0, 1, 1);
+    } else {
+      edges = R(-1, -1, 0) + R(1, -1, 0) + R(-1, 1, 0) + R(1, 1, 0) +
+              R(-1, 0, -1) + R(1, 0, -1) + R(-1, 0, 1) + R(1, 0, 1) +
+              R(0, -1, -1) + R(0, 1, -1) + R(0, -1, 1) + R(0, 1, 1);
+    }
+    rc[sidx(I, J, K, nc)] = (T)0.125 * centre + (T)0.03125 * edges;
   }
 }
 
@@ -2535,25 +2595,32 @@ static Sweeps4 sweeps4(Level& L, int level, bool periodic, int nsweeps, bool zer
   return resid ? kDone : kSwept;
 }
 
+// r_C = restriction of the residual of L, after sweeps that ended black.
 template <typename T>
-static void resid_red(const T* e, const T* r, T* t, const Level& L, T inv_scale, T kappa,
-                      hipStream_t st) {
-  const Box& b = L.box;
-  const int txv = sizeof(T) == 4 ? v4_threads(b) : 0;
-  prof_begin(st, K_RESID_LEVEL);
-  if (txv == 64)
-    hipLaunchKernelGGL((k_resid_red_v4<T, 64>), v4_grid(b, 64), dim3(64, 4), 0, st, e, r, t, L.n, b,
-                       inv_scale, kappa);
-  else if (txv == 32)
-    hipLaunchKernelGGL((k_resid_red_v4<T, 32>), v4_grid(b, 32), dim3(32, 8), 0, st, e, r, t, L.n, b,
-                       inv_scale, kappa);
-  else if (txv == 16)
-    hipLaunchKernelGGL((k_resid_red_v4<T, 16>), v4_grid(b, 16), dim3(16, 16), 0, st, e, r, t, L.n, b,
-                       inv_scale, kappa);
+static void resid_restrict(const Level& L, const Level& C, T inv_scale, T kappa, hipStream_t st) {
+  const Box& bc = C.box;
+  const unsigned gx = (unsigned)((bc.hi[0] - bc.lo[0] + kRrX) / kRrX);
+  const unsigned gy = (unsigned)((bc.hi[1] - bc.lo[1] + kRrY) / kRrY);
+  // deep tiles where they leave four workgroups a compute unit
+  const int nz = bc.hi[2] - bc.lo[2] + 1;
+  const bool deep = gx * gy * (unsigned)((nz + 7) / 8) >= 1024;
+  const dim3 g(gx * gy * (unsigned)(deep ? (nz + 7) / 8 : (nz + 1) / 2)), blk(256);
+  constexpr bool kMay4 = sizeof(T) == 4;
+  const bool v4 = kMay4 && v4_threads(L.box);
+  prof_begin(st, K_RESTRICT);
+#define SDPM_RR(V, CZ)                                                                             \
+  hipLaunchKernelGGL((k_resid_restrict<T, V, CZ>), g, blk, 0, st, (const T*)L.e, (const T*)L.r,    \
+                     (T*)C.r, L.n, C.n, L.box, bc, inv_scale, kappa)
+  if (v4 && deep)
+    SDPM_RR(kMay4, 8);
+  else if (v4)
+    SDPM_RR(kMay4, 2);
+  else if (deep)
+    SDPM_RR(false, 8);
   else
-    hipLaunchKernelGGL(k_resid_red<T>, half_grid(b), dim3(kBoxTx, kBoxTy), 0, st, e, r, t, L.n, b,
-                       inv_scale, kappa);
-  prof_end(st, K_RESID_LEVEL, 2.0 * sizeof(T) * (double)box_cells(b));
+    SDPM_RR(false, 2);
+#undef SDPM_RR
+  prof_end(st, K_RESTRICT, sizeof(T) * (1.5 * (double)box_cells(L.box) + (double)box_cells(bc)));
 }
 
 // r_C = restriction of L's red residual t; the vector form for FP32 levels
@@ -2681,8 +2748,11 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
     const Sweeps4 fused =
         sweeps4<T>(L, l, periodic, pre, zero, scale, inv_diag, st, true, inv_scale, (T)kappa);
     if (fused == kNotFused) sweep_run<T>((T*)L.e, r, L, l, 0, 2 * pre, zero, scale, inv_diag, st);
-    if (fused != kDone) resid_red<T>((const T*)L.e, r, (T*)L.t, L, inv_scale, (T)kappa, st);
     const Level& C = lv[l + 1];
+    if (fused != kDone) {
+      resid_restrict<T>(L, C, inv_scale, (T)kappa, st);
+      continue;
+    }
     prof_begin(st, K_RESTRICT);
     restrict_level<T>(L, C, st);
     prof_end(st, K_RESTRICT, es * (cells / 2 + (double)box_cells(C.box)));

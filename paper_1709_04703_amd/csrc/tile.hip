@@ -22,7 +22,7 @@
 // t (the residual scratch, whose red half alone the other kernels use), the
 // way up reads them there and writes e.
 // The arithmetic of every cell is that of the separate kernels (k_smooth_color
-// and its 4-cell form, k_resid_red, k_restrict, k_prolong, whose 4-cell forms
+// and its 4-cell form, k_resid_red_v4, k_restrict, k_prolong, whose 4-cell forms
 // add in another order: V4), so results are bit-identical.
 // Bound by latency: all loads of a thread go out before the first is used, and
 // a half sweep's LDS reads before its writes (the other colour is not written
