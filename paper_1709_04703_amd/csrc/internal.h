@@ -315,6 +315,10 @@ void launch_compact(const ParticleArgs& pa, const double* x_obs, double r2, void
 // + 1 entries): the first sorted index of each block in Morton order, the
 // last entry n.
 size_t sort_scratch_bytes(int64_t capacity);
+// pa.n particles in scratch (three arrays of positions, three of momenta, the
+// ids) back into the arrays of pa.
+template <typename PT>
+void launch_put_back(const ParticleArgs& pa, const void* scratch, hipStream_t st);
 template <typename PT>
 void launch_morton_sort(const ParticleArgs& pa, int ng, double box, int shift, void* sort_scratch,
                         void* particle_scratch, int64_t* block_start, hipStream_t st);

@@ -1187,11 +1187,7 @@ void launch_compact(const ParticleArgs& pa, const double* x_obs, double r2, void
                      x_obs[2], r2, block_offsets, kept_total, sx0, sx1, sx2, sp0, sp1, sp2, sid);
   prof_end(st, K_SCATTER, 2.0 * pbytes);
   prof_begin(st, K_COPY);
-  for (int d = 0; d < 3; ++d) {
-    (void)hipMemcpyAsync(pa.x[d], sx0 + d * n, n * sizeof(double), hipMemcpyDeviceToDevice, st);
-    (void)hipMemcpyAsync(pa.p[d], sp0 + d * n, n * sizeof(PT), hipMemcpyDeviceToDevice, st);
-  }
-  (void)hipMemcpyAsync(pa.id, sid, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st);
+  launch_put_back<PT>(pa, scratch, st);
   prof_end(st, K_COPY, 2.0 * pbytes);
 }
 template void launch_compact<float>(const ParticleArgs&, const double*, double, void*, uint32_t*,

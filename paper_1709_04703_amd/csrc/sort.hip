@@ -8,18 +8,27 @@
 // stable); the sort only makes neighbouring particles touch neighbouring
 // cells, which the LDS-privatised deposit and the interpolation exploit.
 //
-// Radix pass: (1) each workgroup histograms the digit of its kChunk keys in
-// LDS, (2) a device-wide exclusive scan over the digit-major table gives
-// every (digit, workgroup) its output base, (3) each workgroup scatters its
-// keys in order: the rank among equal digits inside a wavefront comes from
-// 8 ballots (one per digit bit), wavefronts and rounds are chained through
-// per-digit counters in LDS, so the pass is stable.
+// Radix pass: (1) each workgroup histograms the digit of its keys in LDS, (2)
+// a device-wide exclusive scan over the digit-major table gives every (digit,
+// workgroup) its output base, (3) each workgroup scatters its keys in order.
+// A wavefront has 64 KPL consecutive keys, in registers: it counts its digits,
+// takes its place behind the wavefronts before it, and goes through its keys by
+// rounds of 64, the rank among equal digits from 8 ballots (one per digit bit)
+// and the digit's next place from a counter of its own in LDS, so the pass is
+// stable and its rounds need no barrier.
+// Bound by the scattered stores, one digit's keys of a workgroup being a run:
+// KPL = 16 makes the runs four times as long and the table four times as small
+// as KPL = 4, but leaves a small sort few workgroups.  5 M keys, a pass: 17 us
+// histogram, 14 scan, 32 scatter (17, 22 and 37 with rounds of 256 keys and
+// four barriers each); 2 M keys: scatter 14.5 us, KPL = 4 13.3.
 #include "internal.h"
 
 namespace sdpm {
 namespace {
 
 constexpr int kDigits = 256;
+// keys from which a lane takes 16 (see above)
+constexpr int64_t kSortWide = 1 << 21;
 
 __device__ inline uint32_t spread3(uint32_t v) {
   // insert two zero bits between the low 10-11 bits of v
@@ -34,7 +43,7 @@ __device__ inline uint32_t spread3(uint32_t v) {
 __global__ void __launch_bounds__(256)
 k_morton_keys(const double* __restrict__ x0, const double* __restrict__ x1,
               const double* __restrict__ x2, int64_t n, double inv_h, int ng, int shift,
-              uint32_t* __restrict__ key, uint32_t* __restrict__ val) {
+              uint32_t* __restrict__ key) {
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q >= n) return;
   int c[3];
@@ -48,7 +57,6 @@ k_morton_keys(const double* __restrict__ x0, const double* __restrict__ x1,
   const uint32_t block = spread3((uint32_t)(c[0] >> shift)) | (spread3((uint32_t)(c[1] >> shift)) << 1) |
                          (spread3((uint32_t)(c[2] >> shift)) << 2);
   key[q] = (block << (2 * shift)) | (((uint32_t)c[2] & in) << shift) | ((uint32_t)c[1] & in);
-  val[q] = (uint32_t)q;
 }
 
 // First sorted index of each block (Morton index m): the lower bound of its
@@ -74,6 +82,7 @@ k_block_starts(const uint32_t* __restrict__ key, int64_t n, int shift, int64_t n
   start[m] = lo;
 }
 
+template <int KPL>
 __global__ void __launch_bounds__(256)
 k_radix_hist(const uint32_t* __restrict__ key, int64_t n, int bit, int nblocks,
              uint32_t* __restrict__ hist) {
@@ -81,33 +90,53 @@ k_radix_hist(const uint32_t* __restrict__ key, int64_t n, int bit, int nblocks,
   const int tid = threadIdx.x;
   h[tid] = 0;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kChunk;
-  for (int u = 0; u < kChunk / 256; ++u) {
-    const int64_t q = base + u * 256 + tid;
-    if (q < n) atomicAdd(&h[(key[q] >> bit) & 0xff], 1u);
-  }
+  const int64_t base = (int64_t)blockIdx.x * (256 * KPL);
+  uint32_t k[KPL];
+#pragma unroll
+  for (int u = 0; u < KPL; ++u) k[u] = key[min(base + u * 256 + tid, n - 1)];
+#pragma unroll
+  for (int u = 0; u < KPL; ++u)
+    if (base + u * 256 + tid < n) atomicAdd(&h[(k[u] >> bit) & 0xff], 1u);
   __syncthreads();
   hist[(int64_t)tid * nblocks + blockIdx.x] = h[tid];
 }
 
-template <bool HAS_VAL>
+// val == nullptr: key q has the value q
+template <int KPL>
 __global__ void __launch_bounds__(256)
 k_radix_scatter(const uint32_t* __restrict__ key, const uint32_t* __restrict__ val, int64_t n,
                 int bit, int nblocks, const uint32_t* __restrict__ base_tab,
                 uint32_t* __restrict__ key_out, uint32_t* __restrict__ val_out) {
-  __shared__ uint32_t whist[4][kDigits];
-  __shared__ uint32_t run[kDigits];
+  __shared__ uint32_t run[4][kDigits];           // each wavefront's next place per digit
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  run[tid] = base_tab[(int64_t)tid * nblocks + blockIdx.x];
   const unsigned long long lt = (1ull << lane) - 1ull;
-  const int64_t base = (int64_t)blockIdx.x * kChunk;
-  for (int u = 0; u < kChunk / 256; ++u) {
-    const int64_t q = base + u * 256 + tid;
-    const bool valid = q < n;
-    const uint32_t k = valid ? key[q] : 0u;
-    const uint32_t d = (k >> bit) & 0xff;
-    for (int w = 0; w < 4; ++w) whist[w][tid] = 0;
-    __syncthreads();
+  const int64_t base = ((int64_t)blockIdx.x * 4 + wave) * (64 * KPL) + lane;
+  uint32_t k[KPL], v[KPL];
+#pragma unroll
+  for (int u = 0; u < KPL; ++u) {
+    const int64_t q = min(base + u * 64, n - 1);
+    k[u] = key[q];
+    v[u] = val ? val[q] : (uint32_t)q;
+  }
+  uint32_t start = base_tab[(int64_t)tid * nblocks + blockIdx.x];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) run[w][tid] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < KPL; ++u)
+    if (base + u * 64 < n) atomicAdd(&run[wave][(k[u] >> bit) & 0xff], 1u);
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const uint32_t c = run[w][tid];
+    run[w][tid] = start;
+    start += c;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < KPL; ++u) {
+    const bool valid = base + u * 64 < n;
+    const uint32_t d = (k[u] >> bit) & 0xff;
     // lanes of this wave holding the same digit
     unsigned long long same = __ballot(valid);
     for (int b = 0; b < 8; ++b) {
@@ -115,34 +144,46 @@ k_radix_scatter(const uint32_t* __restrict__ key, const uint32_t* __restrict__ v
       same &= ((d >> b) & 1u) ? m : ~m;
     }
     const uint32_t rank = (uint32_t)__popcll(same & lt);
-    if (valid && rank == 0) whist[wave][d] = (uint32_t)__popcll(same);
-    __syncthreads();
+    // the first of them moves the counter on for all
+    uint32_t at = 0;
+    if (valid && rank == 0) at = atomicAdd(&run[wave][d], (uint32_t)__popcll(same));
+    at = __shfl(at, valid ? __ffsll((unsigned long long)same) - 1 : lane);
     if (valid) {
-      uint32_t off = run[d];
-      for (int w = 0; w < wave; ++w) off += whist[w][d];
-      const uint32_t dst = off + rank;
-      key_out[dst] = k;
-      if (HAS_VAL) val_out[dst] = val[q];
+      key_out[at + rank] = k[u];
+      val_out[at + rank] = v[u];
     }
-    __syncthreads();
-    run[tid] += whist[0][tid] + whist[1][tid] + whist[2][tid] + whist[3][tid];
-    __syncthreads();
   }
 }
 
 // device-wide exclusive scan of uint32 (three kernels)
 constexpr int kScanSeg = 4096;
 
+// a thread has kScanPer consecutive values, a workgroup 256 threads' worth
+constexpr int kScanPer = kScanSeg / 256;
+
+__device__ inline void scan_load(const uint32_t* a, int64_t n, int64_t q, uint32_t (&v)[kScanPer]) {
+  if (q + kScanPer <= n) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+    for (int u = 0; u < kScanPer; u += 4) {
+      const u32x4 x = *(const u32x4*)(a + q + u);
+      v[u] = x[0], v[u + 1] = x[1], v[u + 2] = x[2], v[u + 3] = x[3];
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < kScanPer; ++u) v[u] = q + u < n ? a[q + u] : 0u;
+  }
+}
+
 __global__ void __launch_bounds__(256)
 k_scan_seg_sum(const uint32_t* __restrict__ a, int64_t n, uint32_t* __restrict__ part) {
   __shared__ uint32_t sh[4];
   const int tid = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * kScanSeg;
+  uint32_t v[kScanPer];
+  scan_load(a, n, (int64_t)blockIdx.x * kScanSeg + tid * kScanPer, v);
   uint32_t s = 0;
-  for (int u = 0; u < kScanSeg / 256; ++u) {
-    const int64_t q = base + u * 256 + tid;
-    if (q < n) s += a[q];
-  }
+#pragma unroll
+  for (int u = 0; u < kScanPer; ++u) s += v[u];
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
   if ((tid & 63) == 0) sh[tid >> 6] = s;
   __syncthreads();
@@ -176,24 +217,25 @@ __global__ void __launch_bounds__(256)
 k_scan_apply(uint32_t* __restrict__ a, int64_t n, const uint32_t* __restrict__ part) {
   __shared__ uint32_t wtot[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t base = (int64_t)blockIdx.x * kScanSeg;
-  uint32_t run = part[blockIdx.x];
-  for (int u = 0; u < kScanSeg / 256; ++u) {
-    const int64_t q = base + u * 256 + tid;
-    const uint32_t v = q < n ? a[q] : 0u;
-    // inclusive wave scan
-    uint32_t x = v;
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t y = __shfl_up(x, off, 64);
-      if (lane >= off) x += y;
-    }
-    if (lane == 63) wtot[wave] = x;
-    __syncthreads();
-    uint32_t woff = 0;
-    for (int w = 0; w < wave; ++w) woff += wtot[w];
-    if (q < n) a[q] = run + woff + x - v;
-    run += wtot[0] + wtot[1] + wtot[2] + wtot[3];
-    __syncthreads();
+  const int64_t q = (int64_t)blockIdx.x * kScanSeg + tid * kScanPer;
+  uint32_t v[kScanPer], own = 0;
+  scan_load(a, n, q, v);
+#pragma unroll
+  for (int u = 0; u < kScanPer; ++u) own += v[u];
+  // inclusive wave scan of the threads' sums
+  uint32_t x = own;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(x, off, 64);
+    if (lane >= off) x += y;
+  }
+  if (lane == 63) wtot[wave] = x;
+  __syncthreads();
+  uint32_t run = part[blockIdx.x] + x - own;
+  for (int w = 0; w < wave; ++w) run += wtot[w];
+#pragma unroll
+  for (int u = 0; u < kScanPer; ++u) {
+    if (q + u < n) a[q + u] = run;
+    run += v[u];
   }
 }
 
@@ -214,6 +256,27 @@ k_gather(ParticleArgs pa, const uint32_t* __restrict__ perm, double* __restrict_
   sid[q] = pa.id[s];
 }
 
+// A particle set in scratch back into its arrays, all seven in one launch (5 M
+// particles: 71 us, the rate of a copy; seven copies by the runtime leave a gap
+// after each).
+template <typename PT>
+__global__ void __launch_bounds__(256)
+k_put_back(ParticleArgs pa, const double* __restrict__ sx, const PT* __restrict__ sp,
+           const uint32_t* __restrict__ sid) {
+  const int64_t base = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t q = base + 256 * u;
+    if (q >= pa.n) return;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      pa.x[d][q] = __builtin_nontemporal_load(sx + d * pa.n + q);
+      ((PT*)pa.p[d])[q] = __builtin_nontemporal_load(sp + d * pa.n + q);
+    }
+    pa.id[q] = __builtin_nontemporal_load(sid + q);
+  }
+}
+
 void device_scan(uint32_t* a, int64_t n, uint32_t* part, hipStream_t st) {
   const int64_t np = (n + kScanSeg - 1) / kScanSeg;
   hipLaunchKernelGGL(k_scan_seg_sum, dim3((unsigned)np), dim3(256), 0, st, a, n, part);
@@ -221,18 +284,29 @@ void device_scan(uint32_t* a, int64_t n, uint32_t* part, hipStream_t st) {
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)np), dim3(256), 0, st, a, n, part);
 }
 
-// Sorts by key bits [from, to); the result is in k0, v0 (swapped on the way).
-void radix_sort(uint32_t*& k0, uint32_t*& v0, uint32_t*& k1, uint32_t*& v1, int64_t n, int from, int to,
-                uint32_t* hist, uint32_t* part, hipStream_t st) {
-  const int64_t nb = (n + kChunk - 1) / kChunk;
+// Sorts keys k0 with the values 0 .. n - 1 by key bits [from, to), to > from;
+// the result is in k0, v0 (swapped on the way).
+template <int KPL>
+void radix_passes(uint32_t*& k0, uint32_t*& v0, uint32_t*& k1, uint32_t*& v1, int64_t n, int from,
+                  int to, uint32_t* hist, uint32_t* part, hipStream_t st) {
+  const int64_t nb = (n + 256 * KPL - 1) / (256 * KPL);
   for (int bit = from; bit < to; bit += 8) {
-    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(256), 0, st, k0, n, bit, (int)nb, hist);
+    hipLaunchKernelGGL(k_radix_hist<KPL>, dim3((unsigned)nb), dim3(256), 0, st, k0, n, bit, (int)nb,
+                       hist);
     device_scan(hist, nb * kDigits, part, st);
-    hipLaunchKernelGGL((k_radix_scatter<true>), dim3((unsigned)nb), dim3(256), 0, st, k0, v0, n, bit,
-                       (int)nb, hist, k1, v1);
+    hipLaunchKernelGGL(k_radix_scatter<KPL>, dim3((unsigned)nb), dim3(256), 0, st, k0,
+                       bit == from ? nullptr : v0, n, bit, (int)nb, hist, k1, v1);
     std::swap(k0, k1);
     std::swap(v0, v1);
   }
+}
+
+void radix_sort(uint32_t*& k0, uint32_t*& v0, uint32_t*& k1, uint32_t*& v1, int64_t n, int from, int to,
+                uint32_t* hist, uint32_t* part, hipStream_t st) {
+  if (n >= kSortWide)
+    radix_passes<16>(k0, v0, k1, v1, n, from, to, hist, part, st);
+  else
+    radix_passes<4>(k0, v0, k1, v1, n, from, to, hist, part, st);
 }
 
 __global__ void __launch_bounds__(256)
@@ -249,6 +323,16 @@ k_far_pairs(ParticleArgs pa, double inv_h, int ng, uint32_t* __restrict__ count)
 }
 
 }  // namespace
+
+template <typename PT>
+void launch_put_back(const ParticleArgs& pa, const void* scratch, hipStream_t st) {
+  const double* sx = (const double*)scratch;
+  const PT* sp = (const PT*)(sx + 3 * pa.n);
+  hipLaunchKernelGGL(k_put_back<PT>, dim3((unsigned)((pa.n + 1023) / 1024)), dim3(256), 0, st, pa, sx,
+                     sp, (const uint32_t*)(sp + 3 * pa.n));
+}
+template void launch_put_back<float>(const ParticleArgs&, const void*, hipStream_t);
+template void launch_put_back<double>(const ParticleArgs&, const void*, hipStream_t);
 
 void launch_far_pairs(const ParticleArgs& pa, int ng, double box, uint32_t* count, hipStream_t st) {
   const int64_t pairs = (pa.n + 63) / 64;
@@ -271,7 +355,7 @@ void launch_block_order(const ParticleArgs& pa, int ng, double box, void* scratc
   while ((1 << lg) < nb1) ++lg;
   prof_begin(st, K_SORT);
   hipLaunchKernelGGL(k_morton_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pa.x[0],
-                     pa.x[1], pa.x[2], n, (double)ng / box, ng, kBlkShift, k0, v0);
+                     pa.x[1], pa.x[2], n, (double)ng / box, ng, kBlkShift, k0);
   // the blocks alone: the order inside one is free
   radix_sort(k0, v0, k1, v1, n, 2 * kBlkShift, 2 * kBlkShift + 3 * lg, hist, part, st);
   hipLaunchKernelGGL(k_block_starts, dim3((unsigned)((nblk + 256) / 256)), dim3(256), 0, st, k0, n,
@@ -308,7 +392,7 @@ void launch_morton_sort(const ParticleArgs& pa, int ng, double box, int shift, v
   const unsigned gp = (unsigned)((n + 255) / 256);
   prof_begin(st, K_SORT);
   hipLaunchKernelGGL(k_morton_keys, dim3(gp), dim3(256), 0, st, pa.x[0], pa.x[1], pa.x[2], n,
-                     (double)ng / box, ng, shift, k0, v0);
+                     (double)ng / box, ng, shift, k0);
   radix_sort(k0, v0, k1, v1, n, 0, bits, hist, part, st);
   if (block_start) {
     const int64_t nb1 = ng >> shift, nblk = nb1 * nb1 * nb1;
@@ -331,11 +415,7 @@ void launch_morton_sort(const ParticleArgs& pa, int ng, double box, int shift, v
                      sid);
   prof_end(st, K_GATHER, 2.0 * pbytes + 4.0 * n);
   prof_begin(st, K_COPY);
-  for (int d = 0; d < 3; ++d) {
-    (void)hipMemcpyAsync(pa.x[d], sx0 + d * n, n * sizeof(double), hipMemcpyDeviceToDevice, st);
-    (void)hipMemcpyAsync(pa.p[d], sp0 + d * n, n * sizeof(PT), hipMemcpyDeviceToDevice, st);
-  }
-  (void)hipMemcpyAsync(pa.id, sid, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st);
+  launch_put_back<PT>(pa, particle_scratch, st);
   prof_end(st, K_COPY, 2.0 * pbytes);
 }
 template void launch_morton_sort<float>(const ParticleArgs&, int, double, int, void*, void*,
