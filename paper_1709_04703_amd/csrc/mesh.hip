@@ -1030,7 +1030,7 @@ k_sweep4(const T* __restrict__ ein, T* __restrict__ eout, const T* __restrict__ 
   const int nc = hn, mc = nc - 1, X0 = (H0 - 4 + 4 * u) & hm;
   const int J[2] = {jj >> 1, ((jj + 1) >> 1) & mc};
   const bool dy = jj & 1;
-  T csum[PROL ? 5 : 1], cq[2][PROL ? 5 : 1];
+  T csum[5], cq[2][5];
   auto ld_c = [&](int z) {                       // rows of plane (z + 1) / 2
     const int K = (((z & m) + 1) >> 1) & mc;
 #pragma unroll
@@ -2532,27 +2532,29 @@ void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag
 #undef SDPM_SWEEP4P
     return;
   }
-  if (!first && e != e_out)
-    hipMemcpyAsync(e_out, e, (size_t)n * n * n * sizeof(T), hipMemcpyDeviceToDevice, st);
-  Level L{};
-  L.n = n;
-  L.box = b;
-  sweep_run<T>(e_out, r, L, 1, 0, 4, first, scale, inv_diag, st);
-  if (t) {
-    const int txv = v4_threads(b);
-    const dim3 g = v4_grid(b, txv);
-    if (txv == 64)
-      hipLaunchKernelGGL((k_resid_red_v4<T, 64>), g, dim3(64, 4), 0, st, e_out, r, t, n, b,
-                         inv_scale, kappa);
-    else if (txv == 32)
-      hipLaunchKernelGGL((k_resid_red_v4<T, 32>), g, dim3(32, 8), 0, st, e_out, r, t, n, b,
-                         inv_scale, kappa);
-    else
-      hipLaunchKernelGGL((k_resid_red_v4<T, 16>), g, dim3(16, 16), 0, st, e_out, r, t, n, b,
-                         inv_scale, kappa);
+  // separate launches: the FP32 form alone is called for
+  if constexpr (sizeof(T) == 4) {
+    if (!first && e != e_out)
+      (void)hipMemcpyAsync(e_out, e, (size_t)n * n * n * sizeof(T), hipMemcpyDeviceToDevice, st);
+    Level L{};
+    L.n = n;
+    L.box = b;
+    sweep_run<T>(e_out, r, L, 1, 0, 4, first, scale, inv_diag, st);
+    if (t) {
+      const int txv = v4_threads(b);
+      const dim3 g = v4_grid(b, txv);
+      if (txv == 64)
+        hipLaunchKernelGGL((k_resid_red_v4<T, 64>), g, dim3(64, 4), 0, st, e_out, r, t, n, b,
+                           inv_scale, kappa);
+      else if (txv == 32)
+        hipLaunchKernelGGL((k_resid_red_v4<T, 32>), g, dim3(32, 8), 0, st, e_out, r, t, n, b,
+                           inv_scale, kappa);
+      else
+        hipLaunchKernelGGL((k_resid_red_v4<T, 16>), g, dim3(16, 16), 0, st, e_out, r, t, n, b,
+                           inv_scale, kappa);
+    }
   }
 }
-
 template void launch_sweeps4<float>(const float*, float*, const float*, int, float, float, bool, bool,
                                     float*, float, float, const Box*, hipStream_t, const float*);
 template void launch_sweeps4<double>(const double*, double*, const double*, int, double, double, bool,
@@ -2713,7 +2715,6 @@ constexpr int kModesMin = 8;
 template <typename T>
 const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int coarse_sweeps,
                 bool periodic, bool fine_start, hipStream_t st) {
-  const dim3 blk(kBoxTx, kBoxTy);
   const double es = sizeof(T);
   // The hierarchy ends at the first level below the finest whose own sweeps
   // reach the coarsest solve's 1e-3 in at most pre + post + 1 sweeps: with
@@ -2768,7 +2769,7 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
                                   (int64_t)kCoarseMax * kCoarseMax * kCoarseMax);
     const T scale = (T)sc, inv_diag = (T)(1.0 / (6.0 + sc * kappa));
     const int sweeps = std::max(1, std::min(coarse_sweeps, sweeps_for_1e3(L, l, kappa, periodic)));
-    if (periodic && L.n == 16 && sweeps >= kModesMin) {
+    if (sizeof(T) == 8 && periodic && L.n == 16 && sweeps >= kModesMin) {
       prof_begin(st, K_COARSE);
       hipLaunchKernelGGL(k_coarse_modes<T>, dim3(1), dim3(512), 0, st, (T*)L.e, (const T*)L.r, scale,
                          inv_diag, sweeps, kappa == 0.0 ? 1 : 0);
