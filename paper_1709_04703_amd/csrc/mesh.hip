@@ -1603,6 +1603,8 @@ k_prolong_black_v4(const float* __restrict__ ec, float* __restrict__ ef, int nc,
 // that every lane works in every half sweep and consecutive lanes read
 // consecutive entries (cells owned regardless of colour, half of the lanes
 // idle: 79 us in FP32, 89 us in FP64 for 64 sweeps of 16^3, now 45 and 48).
+// (A row per thread, the x neighbours in its registers, the y neighbours by
+// lane shifts and only the z neighbours through LDS: 44 us in FP32.)
 // With project != 0 (periodic, kappa = 0) the mean of r is removed first and
 // the mean of e afterwards.  The host checks that the local array fits.
 constexpr int kCoarsePer = kCoarseMax * kCoarseMax * kCoarseMax / 2048;
@@ -1727,17 +1729,16 @@ __device__ inline double cos16(int m) {
 // Removing the means of r and e is setting the constant mode to 0.
 // The transforms are products by the symmetric 16 x 16 matrix
 // h_kx = (cos + sin)(2 pi k x / 16) / 4, its own inverse, on the FP64 matrix
-// instruction for FP32 levels as well.  A wave takes planes z = w, w + 8 in x
+// instruction.  A wave takes planes z = w, w + 8 in x
 // and y, then rows ky = w, w + 8 in z.  A product's result lies in the
 // registers as the next one's operand (lane l, element q: row l / 16 + 4 q,
 // column l % 16, of the result as of a right operand; the transpose as of a
 // left one), so only the turn from planes to rows and back passes through LDS
 // (rows of 17 doubles: no bank conflicts either way).
 // Bound by latency and by the 48 matrix instructions of each wave: 9 us whatever
-// the sweeps (64 of them in k_coarse: 45 us in FP32, 48 in FP64).
-template <typename T>
+// the sweeps (64 of them in k_coarse: 48 us).
 __global__ void __launch_bounds__(512)
-k_coarse_modes(T* __restrict__ e, const T* __restrict__ r, T scale, T inv_diag, int sweeps,
+k_coarse_modes(double* __restrict__ e, const double* __restrict__ r, double scale, double inv_diag, int sweeps,
                int project) {
   typedef double f64x4 __attribute__((ext_vector_type(4)));
   constexpr int kRow = 17, kPlane = 16 * kRow;
@@ -1747,7 +1748,7 @@ k_coarse_modes(T* __restrict__ e, const T* __restrict__ r, T scale, T inv_diag, 
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) f[t][q] = (double)r[sidx(col, row + 4 * q, w + 8 * t, 16)];
+    for (int q = 0; q < 4; ++q) f[t][q] = r[sidx(col, row + 4 * q, w + 8 * t, 16)];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int a = (row + 4 * q) * col;
@@ -1757,7 +1758,7 @@ k_coarse_modes(T* __restrict__ e, const T* __restrict__ r, T scale, T inv_diag, 
   double mu[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    mu[q] = 2.0 * (cos16(col) + cos16(w) + cos16(row + 4 * q)) * (double)inv_diag;
+    mu[q] = 2.0 * (cos16(col) + cos16(w) + cos16(row + 4 * q)) * inv_diag;
     const double m2 = mu[q] * mu[q];
     double acc = 0.0, pw = 1.0;
     for (int bit = 31 - __clz(sweeps); bit >= 0; --bit) {
@@ -1793,7 +1794,7 @@ k_coarse_modes(T* __restrict__ e, const T* __restrict__ r, T scale, T inv_diag, 
   }
   // mode (col, w, row + 4 q) of f[0]; its partner is f[1][q ^ 2] of lane l ^ 8
   const bool zero_mode = project && threadIdx.x == 0;
-  const double s = (double)scale * (double)inv_diag;
+  const double s = scale * inv_diag;
   f64x4 g[2];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -1818,7 +1819,7 @@ k_coarse_modes(T* __restrict__ e, const T* __restrict__ r, T scale, T inv_diag, 
     f[t] = mul(f[t], h);                         // (ky, x)
     f[t] = mul(h, f[t]);                         // (y, x)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) e[sidx(col, row + 4 * q, w + 8 * t, 16)] = (T)f[t][q];
+    for (int q = 0; q < 4; ++q) e[sidx(col, row + 4 * q, w + 8 * t, 16)] = f[t][q];
   }
 }
 
@@ -2708,8 +2709,10 @@ static bool tiles(const Level& L, int pre, int post) { return pre == 2 && post =
 template <typename T>
 static bool v4_level(const Level& L) { return sizeof(T) == 4 && v4_threads(L.box) != 0; }
 
-// Sweeps from which the periodic 16^3 level is solved mode by mode: 7 of them take
-// k_coarse 9.5 us in FP32 and 10 in FP64, k_coarse_modes takes 9.
+// Sweeps from which the periodic 16^3 level of an FP64 hierarchy is solved mode
+// by mode: 7 of them take k_coarse 10 us, k_coarse_modes takes 9.  FP32 levels
+// sweep (45 us for 64): the modes' rounding is not the sweeps', and through the
+// initial potential it would show in the last bit of FP32 momenta.
 constexpr int kModesMin = 8;
 
 template <typename T>
@@ -2771,8 +2774,8 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
     const int sweeps = std::max(1, std::min(coarse_sweeps, sweeps_for_1e3(L, l, kappa, periodic)));
     if (sizeof(T) == 8 && periodic && L.n == 16 && sweeps >= kModesMin) {
       prof_begin(st, K_COARSE);
-      hipLaunchKernelGGL(k_coarse_modes<T>, dim3(1), dim3(512), 0, st, (T*)L.e, (const T*)L.r, scale,
-                         inv_diag, sweeps, kappa == 0.0 ? 1 : 0);
+      hipLaunchKernelGGL(k_coarse_modes, dim3(1), dim3(512), 0, st, (double*)L.e, (const double*)L.r,
+                         (double)scale, (double)inv_diag, sweeps, kappa == 0.0 ? 1 : 0);
       prof_end(st, K_COARSE, 2 * es * (double)box_cells(L.box));
     } else if (fits) {
       prof_begin(st, K_COARSE);
