@@ -2749,8 +2749,10 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
       prof_end(st, l == 0 ? K_SMOOTH : K_SMOOTH_COARSE, (zero ? 3 : 4) * 1.5 * es * cells, zero ? 3 : 4);
       continue;
     }
+    // (a pass with the residual leaves the red half of e unwritten, which only
+    // the red post-sweep makes up for)
     const Sweeps4 fused =
-        sweeps4<T>(L, l, periodic, pre, zero, scale, inv_diag, st, true, inv_scale, (T)kappa);
+        sweeps4<T>(L, l, periodic, pre, zero, scale, inv_diag, st, post > 0, inv_scale, (T)kappa);
     if (fused == kNotFused) sweep_run<T>((T*)L.e, r, L, l, 0, 2 * pre, zero, scale, inv_diag, st);
     const Level& C = lv[l + 1];
     if (fused != kDone) {

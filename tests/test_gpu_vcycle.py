@@ -75,3 +75,11 @@ def test_one_cycle(ng, levels, pre, post, kappa, prec):
     tol = 16 * (cfg.coarse_sweeps + levels * (pre + post)) * eps * np.abs(want).max()
     assert np.abs(sim.phi_numpy() - want).max() <= tol
     sim.close()
+
+
+# no sweep after the prolongation, which then adds to both colours of what the
+# pre-smoothing left: on meshes with a second correction array and without
+@pytest.mark.parametrize("ng,levels", [(64, 3), (128, 4), (256, 5)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_one_cycle_without_post_smoothing(ng, levels, prec):
+    test_one_cycle(ng, levels, 2, 0, 1e-4, prec)
