@@ -26,8 +26,12 @@
 // memory without holding the others up: the output wave mails the last
 // plane's new rows to the next workgroup through global memory, the input
 // wave fetches the mail of the workgroup before.  A workgroup waits only on
-// the ones before it, which the hardware dispatches earlier, so every wait
-// ends however many workgroups fit the card.  The sweep takes about ny + nz
+// the ones before it, and draws its place in that order from a counter when it
+// starts: those before it then run already or are done, and every wait ends in
+// whatever order the workgroups are dispatched and whatever else is on the card
+// (with the place taken from the block index, several sweeps at a time could
+// fill an XCD with waiting workgroups of which each sweep's next one needs a
+// compute unit there).  The sweep takes about ny + nz
 // steps of one row and the mail's way (about 4 us) per workgroup, instead of
 // ny + nz - 1 dependent launches: 0.18 ms per sweep at 128^3, 0.59 at 256^3,
 // 2.97 at 512^3, against 1.1, 2.2 and 8.5 ms.  (Barriers per row and the rows
@@ -266,7 +270,8 @@ constexpr int kAdeR = 2;        // rows of the rings between a workgroup's waves
 
 template <int L, int T, int D, bool FWD, bool PER>
 __global__ void __launch_bounds__(64 * (T + 2))
-k_ade_march(double* phi, const double* f, int n, Box b, double lam, uint64_t* mail) {
+k_ade_march(double* phi, const double* f, int n, Box b, double lam, uint64_t* mail,
+            unsigned int* ticket) {
   // stage 0 is fed by the input wave with the rows of the plane before this
   // workgroup's first, stage w + 1 by wave w; cell q of lane l at [q][l].  made[s] and
   // taken[s] count the rows put into stage s and read from it.
@@ -275,16 +280,18 @@ k_ade_march(double* phi, const double* f, int n, Box b, double lam, uint64_t* ma
   constexpr int kRow = L * 64;
   __shared__ double rows[(2 * kAdeIn + (T - 1) * kAdeR) * kRow];
   constexpr int kOut = kAdeIn * kRow, kInner = 2 * kOut;   // after the input ring
-  __shared__ int made[T + 1], taken[T + 1];
+  __shared__ int made[T + 1], taken[T + 1], place;
   constexpr int dir = FWD ? 1 : -1;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nx = b.hi[0] - b.lo[0] + 1, ny = b.hi[1] - b.lo[1] + 1, nz = b.hi[2] - b.lo[2] + 1;
   const int m = n - 1;
-  const int k0 = (int)blockIdx.x * T, kk = k0 + w;   // this wave's plane, counted along the sweep
-  const int last = min(T, nz - k0) - 1;          // this workgroup's last wave with a plane
-  const bool next = blockIdx.x + 1 < gridDim.x;  // then all T waves have one
   if (threadIdx.x <= T) made[threadIdx.x] = taken[threadIdx.x] = 0;
+  if (threadIdx.x == 0) place = gridDim.x > 1 ? (int)atomicAdd(ticket, 1u) : 0;
   __syncthreads();
+  const int group = __builtin_amdgcn_readfirstlane(place);   // this workgroup's place in the sweep
+  const int k0 = group * T, kk = k0 + w;         // this wave's plane, counted along the sweep
+  const int last = min(T, nz - k0) - 1;          // this workgroup's last wave with a plane
+  const bool next = group + 1 < (int)gridDim.x;  // then all T waves have one
   const int i_first = FWD ? b.lo[0] : b.hi[0];
   // offsets of plane kr and, in a plane, of row jr, wrapped if periodic
   auto plane_at = [&](int kr) -> int64_t {
@@ -332,10 +339,9 @@ k_ade_march(double* phi, const double* f, int n, Box b, double lam, uint64_t* ma
     // input: plane k0 - 1, new, from the workgroup before's mail (workgroup 0:
     // the exterior, or on the periodic mesh plane nz - 1, old until the last
     // workgroup, which comes after this one, writes it)
-    if (blockIdx.x > 0) {
-      mail_to_ring<L, kAdeGet, kAdeIn>(mail1 + ((int64_t)blockIdx.x - 1) * box_words, lane_last + 1, ny,
-                                       lane,
-                                       rows, &made[0], &taken[0]);
+    if (group > 0) {
+      mail_to_ring<L, kAdeGet, kAdeIn>(mail1 + ((int64_t)group - 1) * box_words, lane_last + 1, ny,
+                                       lane, rows, &made[0], &taken[0]);
       return;
     }
     const double* p = phi + plane_at(k0 - 1);
@@ -354,7 +360,7 @@ k_ade_march(double* phi, const double* f, int n, Box b, double lam, uint64_t* ma
   }
   if (w == T + 1 && next) {
     // output: mails wave T - 1's rows
-    uint64_t* box = mail1 + (int64_t)blockIdx.x * box_words;
+    uint64_t* box = mail1 + (int64_t)group * box_words;
     for (int k = 0; k < ny; ++k) {
       while (count_get(&made[T]) <= k) __builtin_amdgcn_s_sleep(1);
       double v[L];
@@ -477,28 +483,34 @@ k_ade_march(double* phi, const double* f, int n, Box b, double lam, uint64_t* ma
   }
 }
 
-__global__ void __launch_bounds__(256) k_ade_clear(uint64_t* mail, int64_t words) {
+__global__ void __launch_bounds__(256)
+k_ade_clear(uint64_t* mail, int64_t words, unsigned int* ticket) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0u;
   for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < words; q += (int64_t)gridDim.x * 256)
     mail[q] = 0u;
 }
 
 template <int L, int T, int D>
 void ade_march(double* phi, const double* f, int n, const Box& b, int periodic, double lam,
-               bool forward, uint64_t* mail, hipStream_t st) {
+               bool forward, uint64_t* mail, unsigned int* ticket, hipStream_t st) {
   const int64_t nx = b.hi[0] - b.lo[0] + 1, ny = b.hi[1] - b.lo[1] + 1, nz = b.hi[2] - b.lo[2] + 1;
   const dim3 grid((unsigned)((nz + T - 1) / T)), block(64 * (T + 2));
   const int64_t words = 2 * ((nx + L - 1) / L * L) * ny * ((int64_t)grid.x - (periodic ? 0 : 1));
   if (words > 0)
     hipLaunchKernelGGL(k_ade_clear, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 2048)),
-                       dim3(256), 0, st, mail, words);
+                       dim3(256), 0, st, mail, words, ticket);
   if (periodic && forward)
-    hipLaunchKernelGGL((k_ade_march<L, T, D, true, true>), grid, block, 0, st, phi, f, n, b, lam, mail);
+    hipLaunchKernelGGL((k_ade_march<L, T, D, true, true>), grid, block, 0, st, phi, f, n, b, lam, mail,
+                       ticket);
   else if (periodic)
-    hipLaunchKernelGGL((k_ade_march<L, T, D, false, true>), grid, block, 0, st, phi, f, n, b, lam, mail);
+    hipLaunchKernelGGL((k_ade_march<L, T, D, false, true>), grid, block, 0, st, phi, f, n, b, lam, mail,
+                       ticket);
   else if (forward)
-    hipLaunchKernelGGL((k_ade_march<L, T, D, true, false>), grid, block, 0, st, phi, f, n, b, lam, mail);
+    hipLaunchKernelGGL((k_ade_march<L, T, D, true, false>), grid, block, 0, st, phi, f, n, b, lam, mail,
+                       ticket);
   else
-    hipLaunchKernelGGL((k_ade_march<L, T, D, false, false>), grid, block, 0, st, phi, f, n, b, lam, mail);
+    hipLaunchKernelGGL((k_ade_march<L, T, D, false, false>), grid, block, 0, st, phi, f, n, b, lam, mail,
+                       ticket);
 }
 
 template <int L>
@@ -521,20 +533,20 @@ void ade_diagonals(double* phi, const double* f, int n, const Box& b, int period
 }  // namespace
 
 void launch_ade_sweep(double* phi, const double* f, int n, const Box& b, bool periodic, double lam,
-                      bool forward, void* scratch, hipStream_t st) {
+                      bool forward, void* scratch, unsigned int* ticket, hipStream_t st) {
   const int nx = b.hi[0] - b.lo[0] + 1;
   const int per = periodic ? 1 : 0;
   prof_begin(st, K_ADE);
   // T planes per workgroup (with the input and the output wave 8 waves, two per
   // SIMD, 256 registers each) and D rows of prefetch, as many as these take
   if (nx <= 64)
-    ade_march<1, 6, 6>(phi, f, n, b, per, lam, forward, (uint64_t*)scratch, st);
+    ade_march<1, 6, 6>(phi, f, n, b, per, lam, forward, (uint64_t*)scratch, ticket, st);
   else if (nx <= 128)
-    ade_march<2, 6, 6>(phi, f, n, b, per, lam, forward, (uint64_t*)scratch, st);
+    ade_march<2, 6, 6>(phi, f, n, b, per, lam, forward, (uint64_t*)scratch, ticket, st);
   else if (nx <= 256)
-    ade_march<4, 6, 4>(phi, f, n, b, per, lam, forward, (uint64_t*)scratch, st);
+    ade_march<4, 6, 4>(phi, f, n, b, per, lam, forward, (uint64_t*)scratch, ticket, st);
   else if (nx <= 512)
-    ade_march<8, 6, 2>(phi, f, n, b, per, lam, forward, (uint64_t*)scratch, st);
+    ade_march<8, 6, 2>(phi, f, n, b, per, lam, forward, (uint64_t*)scratch, ticket, st);
   else if (nx <= 1024)
     ade_diagonals<16>(phi, f, n, b, per, lam, forward, st);
   else

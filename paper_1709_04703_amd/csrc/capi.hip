@@ -24,7 +24,7 @@ struct sdpm_ctx {
   Level lv[kMaxLevels];
   double* partial = nullptr;
   double* dscal = nullptr;      // reduction outputs
-  uint32_t* dflags = nullptr;   // [0] error flags, [1] removed count
+  uint32_t* dflags = nullptr;   // [0] error flags, [1] removed count, [kAdeTicket]
   uint64_t* dkept = nullptr;
   uint32_t* bcounts = nullptr;
   uint32_t* boffsets = nullptr;
@@ -1245,7 +1245,7 @@ int sdpm_step(sdpm_ctx* c, double a, double da, sdpm_step_stats* out) {
   if (ade) {
     // the paper's ADE: a forward sweep with the mid-step source f = rhs
     launch_ade_sweep(c->fields.phi, c->fields.rhs, g.ng, c->lv[0].box, c->periodic != 0,
-                     1.0 / sc.kappa1_h2, true, c->lv[0].r, c->st);
+                     1.0 / sc.kappa1_h2, true, c->lv[0].r, c->dflags + kAdeTicket, c->st);
   } else {
     src1 = solve(c, sc.kappa1_h2, 0, &s1, rh1);
     if (src1 && src1 != SDPM_ENOCONV) return src1;
@@ -1293,7 +1293,7 @@ int sdpm_step(sdpm_ctx* c, double a, double da, sdpm_step_stats* out) {
   if (ade) {
     // the same source, the sweep in the other direction
     launch_ade_sweep(c->fields.phi, c->fields.rhs, g.ng, c->lv[0].box, c->periodic != 0,
-                     1.0 / sc.kappa2_h2, false, c->lv[0].r, c->st);
+                     1.0 / sc.kappa2_h2, false, c->lv[0].r, c->dflags + kAdeTicket, c->st);
   } else if (sc.kappa2_h2 > 0.0) {
     const bool mg = mg_solve(c);
     if (!rh2_done) rh2 = assemble_rhs(c, sc.s_half, sc.kappa2_h2, 1, mg);
@@ -1481,7 +1481,7 @@ int sdpm_ade_sweep(sdpm_ctx* c, double lam, int forward) {
   if (!(lam > 0.0) || !std::isfinite(lam))
     return fail(c, SDPM_EINVAL, "lam must be finite and > 0");
   launch_ade_sweep(c->fields.phi, c->fields.rhs, c->cfg.ng, c->lv[0].box, c->periodic != 0, lam,
-                   forward != 0, c->lv[0].r, c->st);
+                   forward != 0, c->lv[0].r, c->dflags + kAdeTicket, c->st);
   HIP_TRY(c, hipStreamSynchronize(c->st));
   if (c->prof.on) c->prof.collect();
   return SDPM_OK;

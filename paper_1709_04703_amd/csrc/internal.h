@@ -19,6 +19,8 @@ constexpr int kGateProbe = 8, kGateProbeMax = 256;   // solves skipped by the ne
 constexpr int kNormSlot = 16, kNormRing = 32, kHostNorm = 64, kHostScalars = 128;
 // the four sums of a residual estimate (launch_correct_est), in dscal and hpin
 constexpr int kEstSlot = 4;
+// The device flags' entry that counts the workgroups of an ADE sweep.
+constexpr int kAdeTicket = 8;
 // run-ahead of the outer iterations: at most kMaxAhead without a host wait,
 // and only while the predicted norm exceeds kAheadMargin * threshold
 constexpr int kMaxAhead = 16;
@@ -192,9 +194,10 @@ int power_spectrum(const double* const x[3], int64_t npart, double box, int n, i
                    void* ws, hipStream_t st, double* k_out, double* p_out, double* praw_out,
                    int64_t* modes_out, char* msg, size_t len);
 // One ADE sweep of phi over box b with source f (ade.hip); scratch: 4 n^3
-// bytes (rows passed between workgroups).
+// bytes (rows passed between workgroups); ticket: a counter of the sweep's
+// workgroups, cleared here.
 void launch_ade_sweep(double* phi, const double* f, int n, const Box& b, bool periodic, double lam,
-                      bool forward, void* scratch, hipStream_t st);
+                      bool forward, void* scratch, unsigned int* ticket, hipStream_t st);
 // One V-cycle for A_0 e = r_0; returns the level-0 buffer holding e.  With
 // fine_start the cycle improves the e already on level 0 (a further cycle on
 // the same r_0), else it starts from e = 0.  Levels with the fused sweeps

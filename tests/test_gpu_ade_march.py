@@ -78,3 +78,45 @@ def test_ragged_boxes(ng, cells, forward):
     # the bound of the periodic sweep's own test: 64 roundings of the terms
     assert _box_residual(old, new, f, lam, lo, hi, forward) <= 1e-14 * 64 * scale
     sim.close()
+
+
+# Sweeps of several contexts at a time, each on a stream and thread of its own:
+# their workgroups, which wait for one another within a sweep, share the compute
+# units in any order.  Every sweep gives what it gives alone.
+@pytest.mark.parametrize("ng,contexts,sweeps", [(128, 8, 12), (256, 6, 8), (512, 4, 3)])
+def test_concurrent_sweeps(ng, contexts, sweeps):
+    import threading
+
+    import torch
+
+    lam = 8.8
+    cfg = lib_config(ng, 100.0, c_grav=-1.0, precision=0, n_initial=1, solver=1)
+    gen = torch.Generator(device="cuda:0").manual_seed(ng)
+    old = torch.randn((ng,) * 3, generator=gen, dtype=torch.float64, device="cuda:0")
+    f = torch.randn((ng,) * 3, generator=gen, dtype=torch.float64, device="cuda:0")
+    sims = []
+    for _ in range(contexts):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            sims.append(make_sim(cfg, 1))
+    for sim in sims:
+        sim.bind([[50.0, 50.0, 50.0]], [[0.0, 0.0, 0.0]], [0])
+        sim.phi.copy_(old)
+        sim.rhs.copy_(f)
+    torch.cuda.synchronize()
+
+    def run(sim):
+        for q in range(sweeps):
+            sim.ade_sweep(lam, q % 2 == 0)
+
+    threads = [threading.Thread(target=run, args=(sim,)) for sim in sims[1:]]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    run(sims[0])                                 # alone
+    torch.cuda.synchronize()
+    assert not torch.equal(sims[0].phi, old)
+    for sim in sims[1:]:
+        assert torch.equal(sim.phi, sims[0].phi)
+    for sim in sims:
+        sim.close()
