@@ -1128,8 +1128,7 @@ int sdpm_create(const sdpm_config* cfg, void* workspace, int64_t ws_bytes, void*
   }
   clear_all_levels(c);
   if (cfg->solver == SDPM_SOLVER_FFT) {
-    fft_init(&c->fft, cfg->ng, c->fft.c, c->fft.sym, c->st);
-    if (hipGetLastError() != hipSuccess) {
+    if (fft_init(&c->fft, cfg->ng, c->fft.c, c->fft.sym, c->st) != SDPM_OK) {
       for (auto& e : c->ev) (void)hipEventDestroy(e);
       (void)hipHostFree(c->hpin);
       delete c;

@@ -25,7 +25,7 @@
 // time for its plan.
 #include <algorithm>
 #include <cmath>
-#include <cstdio>
+#include <tuple>
 
 #include "internal.h"
 
@@ -276,21 +276,33 @@ __global__ void __launch_bounds__(256) k_fft_tables(c64* __restrict__ tw, double
   sym[k] = 4.0 * h * h;                        // 2 - 2 cos(2 pi k / n) without its cancellation
 }
 
+// The launches' own status: hipGetLastError would also return what another
+// caller left in the thread before.
+template <typename... P, typename... A>
+bool launched(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t st, A... a) {
+  std::tuple<P...> args(a...);
+  return std::apply(
+      [&](auto&... v) {
+        void* at[] = {(void*)&v...};
+        return hipLaunchKernel((const void*)kernel, grid, block, at, 0, st) == hipSuccess;
+      },
+      args);
+}
+
 template <int N, int MODE>
-void cols(const FftPlan& p, bool z, double kappa_h2, hipStream_t st) {
+bool cols(const FftPlan& p, bool z, double kappa_h2, hipStream_t st) {
   constexpr int C = fft_cols(N);
   const int64_t row = p.pitch, plane = (int64_t)p.pitch * N;
   const int hx = N / 2 + 1;
-  hipLaunchKernelGGL((k_fft_cols<N, MODE>), dim3((hx + C - 1) / C, N), dim3(N * C / 8), 0, st,
-                     (c64*)p.c, hx, z ? plane : row, z ? row : plane, (const c64*)p.tw, p.sym,
-                     kappa_h2, 1.0 / ((double)N * N * N));
+  return launched(k_fft_cols<N, MODE>, dim3((hx + C - 1) / C, N), dim3(N * C / 8), st, (c64*)p.c, hx,
+                  z ? plane : row, z ? row : plane, (const c64*)p.tw, p.sym, kappa_h2,
+                  1.0 / ((double)N * N * N));
 }
 template <int N, bool INV>
-void rows(const FftPlan& p, const double* in, double* out, hipStream_t st) {
+bool rows(const FftPlan& p, const double* in, double* out, hipStream_t st) {
   constexpr int R = fft_rows<N>();
-  hipLaunchKernelGGL((k_fft_rows<N, INV>), dim3((N * N + R - 1) / R),
-                     dim3(N >= 16 ? R * N / 16 : 64), 0, st, in, (c64*)p.c, out, p.pitch,
-                     (const c64*)p.tw);
+  return launched(k_fft_rows<N, INV>, dim3((N * N + R - 1) / R), dim3(N >= 16 ? R * N / 16 : 64), st,
+                  in, (c64*)p.c, out, p.pitch, (const c64*)p.tw);
 }
 template <int N>
 void forward_n(const FftPlan& p, const double* in, hipStream_t st) {
@@ -299,19 +311,18 @@ void forward_n(const FftPlan& p, const double* in, hipStream_t st) {
   cols<N, kFwd>(p, true, 0.0, st);
 }
 template <int N>
-void solve_n(const FftPlan& p, const double* rhs, double* phi, double kappa_h2, hipStream_t st) {
+bool solve_n(const FftPlan& p, const double* rhs, double* phi, double kappa_h2, hipStream_t st) {
   const double cells = (double)N * N * N;
   prof_begin(st, K_FFT);
-  rows<N, false>(p, rhs, nullptr, st);
-  cols<N, kFwd>(p, false, 0.0, st);
+  bool ok = rows<N, false>(p, rhs, nullptr, st) && cols<N, kFwd>(p, false, 0.0, st);
   prof_end(st, K_FFT, 32.0 * cells, 2);      // rhs in, the half spectrum out, in and out
   prof_begin(st, K_FFT_DIVIDE);
-  cols<N, kSolve>(p, true, kappa_h2, st);
+  ok = ok && cols<N, kSolve>(p, true, kappa_h2, st);
   prof_end(st, K_FFT_DIVIDE, 16.0 * cells);
   prof_begin(st, K_FFT);
-  cols<N, kInv>(p, false, 0.0, st);
-  rows<N, true>(p, nullptr, phi, st);
+  ok = ok && cols<N, kInv>(p, false, 0.0, st) && rows<N, true>(p, nullptr, phi, st);
   prof_end(st, K_FFT, 32.0 * cells, 2);
+  return ok;
 }
 
 // the padded half spectrum, then the root table
@@ -323,13 +334,14 @@ size_t fft_complex_bytes(int n) { return (size_t)n * n * (n / 2 + 1) * sizeof(c6
 
 // Fits 2 fft_complex_bytes(n), the size the layouts reserve: the padding takes
 // at most 7 of n / 2 + 1 further columns and the table one row.
-void fft_init(FftPlan* p, int n, void* buf, double* sym_dev, hipStream_t st) {
+int fft_init(FftPlan* p, int n, void* buf, double* sym_dev, hipStream_t st) {
   p->n = n;
   p->pitch = fft_pitch(n);
   p->c = buf;
   p->tw = (char*)buf + (size_t)n * n * p->pitch * sizeof(c64);
   p->sym = sym_dev;
-  hipLaunchKernelGGL(k_fft_tables, dim3((n + 255) / 256), dim3(256), 0, st, (c64*)p->tw, p->sym, n);
+  return launched(k_fft_tables, dim3((n + 255) / 256), dim3(256), st, (c64*)p->tw, p->sym, n) ? SDPM_OK
+                                                                                              : SDPM_EHIP;
 }
 
 #define FFT_SIZES(DO) \
@@ -345,11 +357,11 @@ void fft_forward(const FftPlan& p, const double* in, hipStream_t st) {
 
 int fft_solve(const FftPlan& p, const double* rhs, double* phi, double kappa_h2, hipStream_t st) {
   switch (p.n) {
-#define FFT_CASE(N) case N: solve_n<N>(p, rhs, phi, kappa_h2, st); break;
+#define FFT_CASE(N) case N: return solve_n<N>(p, rhs, phi, kappa_h2, st) ? SDPM_OK : SDPM_EHIP;
     FFT_SIZES(FFT_CASE)
 #undef FFT_CASE
   }
-  return hipGetLastError() == hipSuccess ? SDPM_OK : SDPM_EHIP;
+  return SDPM_EINVAL;
 }
 
 }  // namespace sdpm

@@ -183,8 +183,9 @@ struct FftPlan {
   double* sym = nullptr;
 };
 size_t fft_complex_bytes(int n);
-// Sets up p and enqueues the tables' computation.
-void fft_init(FftPlan* p, int n, void* buf, double* sym_dev, hipStream_t st);
+// Sets up p and enqueues the tables' computation.  This and the transforms
+// return SDPM_EHIP when a launch of theirs fails, SDPM_EINVAL for other sizes.
+int fft_init(FftPlan* p, int n, void* buf, double* sym_dev, hipStream_t st);
 // The half spectrum (unnormalised, e^{-i}) of a real n^3 mesh into p.c.
 void fft_forward(const FftPlan& p, const double* in, hipStream_t st);
 int fft_solve(const FftPlan& p, const double* rhs, double* phi, double kappa_h2, hipStream_t st);

@@ -64,3 +64,39 @@ def test_poisson_zero_mode(ng):
     assert float(r.norm() / rhs.norm()) <= 1e-11
     assert abs(float(phi.mean())) <= 1e-12 * float(phi.abs().max())
     sim.close()
+
+
+def test_errors_of_other_callers():
+    """An error that another library left in the thread (refused on the host: a
+    device that does not exist) is not the FFT solver's: contexts are made and
+    solves run as without it."""
+    import ctypes
+
+    import numpy as np
+    import torch
+
+    import paper_1709_04703_amd as P
+
+    ng, kappa = 16, 0.2
+    cfg = lib_config(ng, 100.0, precision=0, n_initial=1, solver=P.SDPM_SOLVER_FFT)
+    sim = make_sim(cfg, 1)
+    phi0 = np.random.default_rng(1).normal(size=(ng,) * 3)
+    sim.bind([[50.0, 50.0, 50.0]], [[0.0, 0.0, 0.0]], [0], phi=phi0)
+    sim.counts.zero_()
+    other = torch.empty_like(sim.workspace)
+    torch.cuda.synchronize()
+    lib = P.library()                           # its symbols include the runtime's
+    ctx = ctypes.c_void_p()
+    try:
+        assert lib.hipSetDevice(1 << 20) != 0
+        sim.solve(kappa, 0.0)
+        assert lib.hipSetDevice(1 << 20) != 0
+        assert lib.sdpm_create(ctypes.byref(cfg), ctypes.c_void_p(other.data_ptr()), sim.ws_bytes,
+                               ctypes.c_void_p(sim.stream.cuda_stream), ctypes.byref(ctx)) == 0
+    finally:
+        lib.hipGetLastError()
+    assert lib.sdpm_destroy(ctx) == 0
+    phi = sim.phi_numpy()
+    lap = sum(np.roll(phi, s, d) for d in range(3) for s in (1, -1)) - 6.0 * phi
+    assert np.abs(lap - kappa * phi + kappa * phi0).max() <= 1e-13 * np.abs(phi0).max()
+    sim.close()
