@@ -305,10 +305,9 @@ bool rows(const FftPlan& p, const double* in, double* out, hipStream_t st) {
                   in, (c64*)p.c, out, p.pitch, (const c64*)p.tw);
 }
 template <int N>
-void forward_n(const FftPlan& p, const double* in, hipStream_t st) {
-  rows<N, false>(p, in, nullptr, st);
-  cols<N, kFwd>(p, false, 0.0, st);
-  cols<N, kFwd>(p, true, 0.0, st);
+bool forward_n(const FftPlan& p, const double* in, hipStream_t st) {
+  return rows<N, false>(p, in, nullptr, st) && cols<N, kFwd>(p, false, 0.0, st) &&
+         cols<N, kFwd>(p, true, 0.0, st);
 }
 template <int N>
 bool solve_n(const FftPlan& p, const double* rhs, double* phi, double kappa_h2, hipStream_t st) {
@@ -347,12 +346,13 @@ int fft_init(FftPlan* p, int n, void* buf, double* sym_dev, hipStream_t st) {
 #define FFT_SIZES(DO) \
   DO(8) DO(16) DO(32) DO(64) DO(128) DO(256) DO(512) DO(1024) DO(2048)
 
-void fft_forward(const FftPlan& p, const double* in, hipStream_t st) {
+int fft_forward(const FftPlan& p, const double* in, hipStream_t st) {
   switch (p.n) {
-#define FFT_CASE(N) case N: forward_n<N>(p, in, st); break;
+#define FFT_CASE(N) case N: return forward_n<N>(p, in, st) ? SDPM_OK : SDPM_EHIP;
     FFT_SIZES(FFT_CASE)
 #undef FFT_CASE
   }
+  return SDPM_EINVAL;
 }
 
 int fft_solve(const FftPlan& p, const double* rhs, double* phi, double kappa_h2, hipStream_t st) {

@@ -187,7 +187,7 @@ size_t fft_complex_bytes(int n);
 // return SDPM_EHIP when a launch of theirs fails, SDPM_EINVAL for other sizes.
 int fft_init(FftPlan* p, int n, void* buf, double* sym_dev, hipStream_t st);
 // The half spectrum (unnormalised, e^{-i}) of a real n^3 mesh into p.c.
-void fft_forward(const FftPlan& p, const double* in, hipStream_t st);
+int fft_forward(const FftPlan& p, const double* in, hipStream_t st);
 int fft_solve(const FftPlan& p, const double* rhs, double* phi, double kappa_h2, hipStream_t st);
 // Power spectrum of particle positions (pk.hip; see sdpm_power_spectrum).
 size_t pk_workspace_bytes(int n);

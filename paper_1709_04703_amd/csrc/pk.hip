@@ -297,8 +297,9 @@ int power_spectrum(const double* const x[3], int64_t npart, double box, int n, i
   hipLaunchKernelGGL(k_pk_delta, dim3(4096), dim3(256), 0, st, mesh, cells,
                      1.0 / (nbar * std::ldexp(1.0, 3 * frac_bits)));
   FftPlan plan;
-  fft_init(&plan, n, base + lay.fft, (double*)(base + lay.sym), st);
-  fft_forward(plan, mesh, st);
+  if (fft_init(&plan, n, base + lay.fft, (double*)(base + lay.sym), st) != SDPM_OK ||
+      fft_forward(plan, mesh, st) != SDPM_OK)
+    return herr("transform failed");
   hipLaunchKernelGGL(k_pk_tables, dim3(((n + 1) * kPkTab + 255) / 256), dim3(256), 0, st, tab, sq, n);
   // shell sums of the raw spectrum
   const double l3 = box * box * box;
