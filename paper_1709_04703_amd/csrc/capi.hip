@@ -1584,8 +1584,14 @@ int sdpm_rb_sweeps(int32_t n, const float* e, float* e_out, const float* r, floa
         return fail(nullptr, SDPM_EINVAL, "rb_sweeps: the box must keep a plane from every face");
     }
   }
-  launch_sweeps4<float>(e, e_out, r, n, scale, inv_diag, first != 0, fused != 0, t_out,
-                 t_out ? 1.0f / scale : 0.0f, kappa_h2, box ? &b : nullptr, (hipStream_t)stream);
+  const Box* const bx = box ? &b : nullptr;
+  const float inv_scale = t_out ? 1.0f / scale : 0.0f;
+  if (fused)
+    launch_sweeps4<float>(e, e_out, r, n, scale, inv_diag, first != 0, t_out, inv_scale, kappa_h2, bx,
+                          (hipStream_t)stream);
+  else
+    launch_separate_sweeps4(e, e_out, r, n, scale, inv_diag, first != 0, t_out, inv_scale, kappa_h2,
+                            bx, (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? SDPM_OK : fail(nullptr, SDPM_EHIP, "rb_sweeps launch failed");
 }
 

@@ -225,21 +225,24 @@ constexpr int kSweep4Min = 128;
 // Cells a side from which an FP32 level has an e_alt array, which the pass with
 // the residual in it needs (128^3: 22 us with it, 13.6 + 4.8 in two launches).
 constexpr int kSweep4Alt = 256;
-// Four colour sweeps (red, black, red, black) of a periodic level of n^3 cells, n a power of two >= 64: with fused, one k_sweep4 pass from e
-// (black colour; not read when first) into e_out (e_out == e allowed only
-// when first); otherwise e copied to e_out (not when first) and four
-// k_smooth_color_v4 launches in place on e_out.  With t (may be null) the
-// red residual of the result goes to t's red half (inv_scale = 1 / scale,
-// kappa = kappa h^2): in the fused pass instead of the red half of e_out,
-// which it then leaves unwritten; otherwise by k_resid_red_v4.
-// The fused pass of an FP64 level takes no t.
+// Four colour sweeps (red, black, red, black) of a periodic level of n^3
+// cells, n a power of two >= 64, in one k_sweep4 pass from e (black colour; not
+// read when first) into e_out (e_out == e allowed only when first).  With t
+// (may be null; FP32 levels only) the red residual of the result goes to t's
+// red half (inv_scale = 1 / scale, kappa = kappa h^2) instead of the red half
+// of e_out, which is then left unwritten.  With coarse (may be null; neither
+// first nor t) e is corrected by the next level's prolonged correction first.
 // With box (may be null: the periodic whole mesh) the sweeps cover a
 // frozen-exterior box that keeps at least one plane from every face of the
 // mesh, e being zero outside it.
 template <typename T>
-void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag, bool first,
-                    bool fused, T* t, T inv_scale, T kappa, const Box* box, hipStream_t st,
-                    const T* coarse = nullptr);
+void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag, bool first, T* t,
+                    T inv_scale, T kappa, const Box* box, hipStream_t st, const T* coarse = nullptr);
+// The same in separate kernels: e copied to e_out (not when first), four
+// colour sweeps in place there, and with t its red residual by k_resid_red_v4.
+void launch_separate_sweeps4(const float* e, float* e_out, const float* r, int n, float scale,
+                             float inv_diag, bool first, float* t, float inv_scale, float kappa,
+                             const Box* box, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Launchers, particle kernels (particles.hip).

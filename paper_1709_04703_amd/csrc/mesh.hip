@@ -2462,105 +2462,103 @@ static int sweep4_chunk(int n, int cols, int nz) {
 static Box whole_mesh(int n) { return Box{{0, 0, 0}, {n - 1, n - 1, n - 1}}; }
 
 template <typename T>
-void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag, bool first,
-                    bool fused, T* t, T inv_scale, T kappa, const Box* box, hipStream_t st,
-                    const T* coarse) {
+void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag, bool first, T* t,
+                    T inv_scale, T kappa, const Box* box, hipStream_t st, const T* coarse) {
   const Box b = box ? *box : whole_mesh(n);
-  if (fused) {
-    // 128 x 32-cell columns (one 768-thread workgroup per compute unit: 138
-    // KB of LDS, 160 KB with the residual); 64 x 32 on a 64^3 mesh
-    // 128-cell columns on periodic levels of 256^3 and up and on boxes in
-    // meshes of 512^3 and up; 64-cell columns (two workgroups per CU) on
-    // smaller meshes and on the boxes of the 256^3 level, where the chunks
-    // of 128-cell columns are short (shrinking phase at 512^3:
-    // 11.5 against 11.7 ms per step; on the periodic 256^3 level the wide
-    // columns win, 0.72 against 0.86 ms per step)
-    const int tx = sizeof(T) == 4 && ((n >= 256 && !box) || n >= 512) ? 128 : 64;
-    const int ux = tx / 8;
-    const int hb = box ? ((b.lo[0] >> 1) & ~3) : 0;
-    const int gx = box ? ((b.hi[0] >> 1) - hb + 4 * ux) / (4 * ux) : n / tx;
-    const int gy = box ? (b.hi[1] - b.lo[1] + 32) / 32 : n / 32;
-    const int nz = b.hi[2] - (coarse ? b.lo[2] & ~1 : b.lo[2]) + 1;
-    const int zc = sweep4_chunk(n, gx * gy, nz);
-    const dim3 g((unsigned)(gx * gy * ((nz + zc - 1) / zc)));
+  // 128 x 32-cell columns (one 768-thread workgroup per compute unit: 138
+  // KB of LDS, 160 KB with the residual); 64 x 32 on a 64^3 mesh
+  // 128-cell columns on periodic levels of 256^3 and up and on boxes in
+  // meshes of 512^3 and up; 64-cell columns (two workgroups per CU) on
+  // smaller meshes and on the boxes of the 256^3 level, where the chunks
+  // of 128-cell columns are short (shrinking phase at 512^3:
+  // 11.5 against 11.7 ms per step; on the periodic 256^3 level the wide
+  // columns win, 0.72 against 0.86 ms per step)
+  const int tx = sizeof(T) == 4 && ((n >= 256 && !box) || n >= 512) ? 128 : 64;
+  const int ux = tx / 8;
+  const int hb = box ? ((b.lo[0] >> 1) & ~3) : 0;
+  const int gx = box ? ((b.hi[0] >> 1) - hb + 4 * ux) / (4 * ux) : n / tx;
+  const int gy = box ? (b.hi[1] - b.lo[1] + 32) / 32 : n / 32;
+  const int nz = b.hi[2] - (coarse ? b.lo[2] & ~1 : b.lo[2]) + 1;
+  const int zc = sweep4_chunk(n, gx * gy, nz);
+  const dim3 g((unsigned)(gx * gy * ((nz + zc - 1) / zc)));
 #define SDPM_SWEEP4P(F, RS, PR, BX, UXX, NTT)                                                       \
   hipLaunchKernelGGL((k_sweep4<T, F, RS, PR, BX, UXX, 32, NTT>), g, dim3(NTT), 0, st, e, e_out, r, n,  \
-                     zc, scale, inv_diag, t, inv_scale, kappa, b, coarse)
+                   zc, scale, inv_diag, t, inv_scale, kappa, b, coarse)
 #define SDPM_SWEEP4(F, RS, BX, UXX, NTT) SDPM_SWEEP4P(F, RS, false, BX, UXX, NTT)
 #define SDPM_SWEEP4_W(BX, UXX, NTT)               \
   do {                                            \
-    if (first && t)                               \
-      SDPM_SWEEP4(true, true, BX, UXX, NTT);      \
-    else if (first)                               \
-      SDPM_SWEEP4(true, false, BX, UXX, NTT);     \
-    else if (t)                                   \
-      SDPM_SWEEP4(false, true, BX, UXX, NTT);     \
-    else if (coarse)                              \
-      SDPM_SWEEP4P(false, false, true, BX, UXX, NTT); \
-    else                                          \
-      SDPM_SWEEP4(false, false, BX, UXX, NTT);    \
+  if (first && t)                               \
+    SDPM_SWEEP4(true, true, BX, UXX, NTT);      \
+  else if (first)                               \
+    SDPM_SWEEP4(true, false, BX, UXX, NTT);     \
+  else if (t)                                   \
+    SDPM_SWEEP4(false, true, BX, UXX, NTT);     \
+  else if (coarse)                              \
+    SDPM_SWEEP4P(false, false, true, BX, UXX, NTT); \
+  else                                          \
+    SDPM_SWEEP4(false, false, BX, UXX, NTT);    \
   } while (0)
-    if constexpr (sizeof(T) == 8) {
-      // no room for the residual's planes in LDS: 64 x 32-cell columns take 154 KB
-      // without them
-      if (box) {
-        if (first)
-          SDPM_SWEEP4(true, false, true, 8, 448);
-        else if (coarse)
-          SDPM_SWEEP4P(false, false, true, true, 8, 448);
-        else
-          SDPM_SWEEP4(false, false, true, 8, 448);
-      } else if (first) {
-        SDPM_SWEEP4(true, false, false, 8, 448);
-      } else if (coarse) {
-        SDPM_SWEEP4P(false, false, true, false, 8, 448);
-      } else {
-        SDPM_SWEEP4(false, false, false, 8, 448);
-      }
-    } else if (tx == 128) {
-      if (box)
-        SDPM_SWEEP4_W(true, 16, 768);
+  if constexpr (sizeof(T) == 8) {
+    // no room for the residual's planes in LDS: 64 x 32-cell columns take 154 KB
+    // without them
+    if (box) {
+      if (first)
+        SDPM_SWEEP4(true, false, true, 8, 448);
+      else if (coarse)
+        SDPM_SWEEP4P(false, false, true, true, 8, 448);
       else
-        SDPM_SWEEP4_W(false, 16, 768);
+        SDPM_SWEEP4(false, false, true, 8, 448);
+    } else if (first) {
+      SDPM_SWEEP4(true, false, false, 8, 448);
+    } else if (coarse) {
+      SDPM_SWEEP4P(false, false, true, false, 8, 448);
     } else {
-      if (box)
-        SDPM_SWEEP4_W(true, 8, 448);
-      else
-        SDPM_SWEEP4_W(false, 8, 448);
+      SDPM_SWEEP4(false, false, false, 8, 448);
     }
+  } else if (tx == 128) {
+    if (box)
+      SDPM_SWEEP4_W(true, 16, 768);
+    else
+      SDPM_SWEEP4_W(false, 16, 768);
+  } else {
+    if (box)
+      SDPM_SWEEP4_W(true, 8, 448);
+    else
+      SDPM_SWEEP4_W(false, 8, 448);
+  }
 #undef SDPM_SWEEP4_W
 #undef SDPM_SWEEP4
 #undef SDPM_SWEEP4P
-    return;
-  }
-  // separate launches: the FP32 form alone is called for
-  if constexpr (sizeof(T) == 4) {
-    if (!first && e != e_out)
-      (void)hipMemcpyAsync(e_out, e, (size_t)n * n * n * sizeof(T), hipMemcpyDeviceToDevice, st);
-    Level L{};
-    L.n = n;
-    L.box = b;
-    sweep_run<T>(e_out, r, L, 1, 0, 4, first, scale, inv_diag, st);
-    if (t) {
-      const int txv = v4_threads(b);
-      const dim3 g = v4_grid(b, txv);
-      if (txv == 64)
-        hipLaunchKernelGGL((k_resid_red_v4<T, 64>), g, dim3(64, 4), 0, st, e_out, r, t, n, b,
-                           inv_scale, kappa);
-      else if (txv == 32)
-        hipLaunchKernelGGL((k_resid_red_v4<T, 32>), g, dim3(32, 8), 0, st, e_out, r, t, n, b,
-                           inv_scale, kappa);
-      else
-        hipLaunchKernelGGL((k_resid_red_v4<T, 16>), g, dim3(16, 16), 0, st, e_out, r, t, n, b,
-                           inv_scale, kappa);
-    }
+}
+template void launch_sweeps4<float>(const float*, float*, const float*, int, float, float, bool, float*,
+                                    float, float, const Box*, hipStream_t, const float*);
+template void launch_sweeps4<double>(const double*, double*, const double*, int, double, double, bool,
+                                     double*, double, double, const Box*, hipStream_t, const double*);
+
+void launch_separate_sweeps4(const float* e, float* e_out, const float* r, int n, float scale,
+                             float inv_diag, bool first, float* t, float inv_scale, float kappa,
+                             const Box* box, hipStream_t st) {
+  const Box b = box ? *box : whole_mesh(n);
+  if (!first && e != e_out)
+    (void)hipMemcpyAsync(e_out, e, (size_t)n * n * n * sizeof(float), hipMemcpyDeviceToDevice, st);
+  Level L{};
+  L.n = n;
+  L.box = b;
+  sweep_run<float>(e_out, r, L, 1, 0, 4, first, scale, inv_diag, st);
+  if (t) {
+    const int txv = v4_threads(b);
+    const dim3 g = v4_grid(b, txv);
+    if (txv == 64)
+      hipLaunchKernelGGL((k_resid_red_v4<float, 64>), g, dim3(64, 4), 0, st, e_out, r, t, n, b,
+                         inv_scale, kappa);
+    else if (txv == 32)
+      hipLaunchKernelGGL((k_resid_red_v4<float, 32>), g, dim3(32, 8), 0, st, e_out, r, t, n, b,
+                         inv_scale, kappa);
+    else
+      hipLaunchKernelGGL((k_resid_red_v4<float, 16>), g, dim3(16, 16), 0, st, e_out, r, t, n, b,
+                         inv_scale, kappa);
   }
 }
-template void launch_sweeps4<float>(const float*, float*, const float*, int, float, float, bool, bool,
-                                    float*, float, float, const Box*, hipStream_t, const float*);
-template void launch_sweeps4<double>(const double*, double*, const double*, int, double, double, bool,
-                                     bool, double*, double, double, const Box*, hipStream_t,
-                                     const double*);
 
 // The fused form of pre or post sweeps on level L when it applies (nsweeps ==
 // 2 red-black pairs, a level of at least kSweep4Min cells a side): from a zero
@@ -2589,7 +2587,7 @@ static Sweeps4 sweeps4(Level& L, int level, bool periodic, int nsweeps, bool zer
   const int id = level > 0 ? K_SWEEP4_COARSE : zero ? K_SWEEP4_FIRST : resid ? K_SWEEP4_RESID : K_SWEEP4;
   prof_begin(st, id);
   launch_sweeps4<T>((const T*)L.e, zero ? (T*)L.e : (T*)alt, (const T*)L.r, L.n, scale, inv_diag, zero,
-                    true, resid ? (T*)L.t : nullptr, inv_scale, kappa, periodic ? nullptr : &L.box, st, coarse);
+                    resid ? (T*)L.t : nullptr, inv_scale, kappa, periodic ? nullptr : &L.box, st, coarse);
   if (!zero) std::swap(L.e, alt);
   // r read, e written (both whole); without the zero guess the black half of
   // e read too; with the residual the red half of t written instead of the
