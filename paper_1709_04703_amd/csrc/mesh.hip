@@ -2546,7 +2546,7 @@ void launch_separate_sweeps4(const float* e, float* e_out, const float* r, int n
   L.box = b;
   sweep_run<float>(e_out, r, L, 1, 0, 4, first, scale, inv_diag, st);
   if (t) {
-    const int txv = v4_threads(b);
+    const int txv = std::max(16, v4_threads(b));   // rows too short for the 4-cell sweeps too
     const dim3 g = v4_grid(b, txv);
     if (txv == 64)
       hipLaunchKernelGGL((k_resid_red_v4<float, 64>), g, dim3(64, 4), 0, st, e_out, r, t, n, b,

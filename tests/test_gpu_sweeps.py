@@ -191,3 +191,12 @@ def test_fused_sweeps_in_place_first():
     P.rb_sweeps(n, None, ref, r, 1.0, 1.0 / 6.0, True, False)
     torch.cuda.synchronize()
     assert torch.equal(e.view(torch.int32), ref.view(torch.int32))
+
+
+# boxes whose rows are too short for the 4-cell kernels; the separate form takes
+# its residual with them all the same
+@pytest.mark.parametrize("lo,hi", [((10, 10, 10), (50, 50, 50)), ((3, 20, 31), (3, 40, 33)),
+                                   ((7, 1, 1), (8, 62, 62))])
+@pytest.mark.parametrize("first", [True, False])
+def test_residual_on_narrow_boxes(lo, hi, first):
+    test_fused_sweeps_on_a_frozen_exterior_box(64, lo, hi, first, True)
