@@ -219,10 +219,7 @@ size_t carve(const sdpm_config& c, int64_t capacity, char* base, sdpm_ctx* ctx) 
       ctx->lv[l].box = full_box(n);
     }
   }
-  const Box fb = full_box(c.ng);
-  const dim3 g = box_grid(fb);
-  const size_t maxblocks = (size_t)g.x * g.y * g.z;
-  double* partial = (double*)take(maxblocks * kReduceSlots * sizeof(double));
+  double* partial = (double*)take((size_t)reduction_blocks(c.ng) * kReduceSlots * sizeof(double));
   double* dscal = (double*)take(64 * sizeof(double));
   uint32_t* dflags = (uint32_t*)take(16 * sizeof(uint32_t));
   uint64_t* dkept = (uint64_t*)take(2 * sizeof(uint64_t));

@@ -169,6 +169,10 @@ bool launch_rhs_residual(const uint64_t* counts, const double* phi, double* rhs,
 void launch_sum_phi(const double* phi, int n, const Box& b, double* partial, int* nblocks,
                     hipStream_t st);
 void launch_add_const(double* phi, float* chg, int n, const Box& b, double v, hipStream_t st);
+// Workgroups of the largest reduction over a box of an n^3 mesh, which size the
+// partials; those of the residual and estimating passes over box b.
+int64_t reduction_blocks(int n);
+int residual_blocks(const Box& b);
 void launch_reduce_final(const double* partial, int nblocks, int nslots, double* out,
                          hipStream_t st);
 // Exact periodic FFT solve of (Lap_h - kappa h^2) phi = rhs (fft.hip) on an

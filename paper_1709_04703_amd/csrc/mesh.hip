@@ -209,9 +209,7 @@ k_residual(const double* __restrict__ phi, const double* __restrict__ rhs, T* __
 #define SDPM_RES_KZ 16
 #endif
 // planes per thread of the FP64 residual's z-march (at 512^3, 16 measured 2 %
-// faster than 8 and 5 % faster than 4); its 256-thread tiles then span at
-// least as many cells as the box kernels', whose grid sizes the reduction
-// partials
+// faster than 8 and 5 % faster than 4)
 constexpr int kResKz = SDPM_RES_KZ;
 // Fewer planes, down to two, where they leave less than kResGrid workgroups:
 // a march is a serial chain of loads, and a small mesh has too few of them to
@@ -219,7 +217,6 @@ constexpr int kResKz = SDPM_RES_KZ;
 // estimate 34 -> 18 us, source and residual 30 -> 16 us; 32^3 in FP64: 31 -> 8 us;
 // 256 workgroups: 22 and 20 us at 128^3, 1024: 16 and 17).
 constexpr int kResKzMin = 2, kResGrid = 512;
-static_assert(kResKzMin >= 2 && kResKz >= kResKzMin, "more residual workgroups than reduction partials");
 // cols: tiles in x and y
 static int res_planes(unsigned cols, const Box& b) {
   int kz = kResKz;
@@ -1960,7 +1957,7 @@ void launch_rhs(const uint64_t* counts, double* phi, double* rhs, int n, const B
 // reaches on full rows (measured on the 512^3 finest level: 4.77, 4.38 and
 // 4.07 TB/s for 64, 32 and 16 threads), so that a box row of 190 entries
 // takes three 64-entry tiles rather than two of 128.
-inline int tile_threads(int ext) {
+static int tile_threads(int ext) {
   const int widths[3] = {64, 32, 16};
   const double rate[3] = {1.0, 0.92, 0.85};
   int best = 16;
@@ -1976,20 +1973,41 @@ inline int tile_threads(int ext) {
   return best;
 }
 
+// The tiles of a box: their width as for the colour sweeps (the extent here in
+// cells, 4 per thread), planes and number.
+struct ResTiles {
+  int txv, kz, blocks;
+};
+static ResTiles res_tiles(const Box& b) {
+  const int ib = b.lo[0] & ~3, txv = tile_threads(b.hi[0] - ib + 1);
+  const unsigned gx = (unsigned)((b.hi[0] - ib + 4 * txv) / (4 * txv));
+  const unsigned gy = (unsigned)((b.hi[1] - b.lo[1] + 256 / txv) / (256 / txv));
+  const int kz = res_planes(gx * gy, b);
+  return {txv, kz, (int)(gx * gy * (unsigned)((b.hi[2] - b.lo[2] + kz) / kz))};
+}
+int residual_blocks(const Box& b) { return res_tiles(b).blocks; }
+// A box kernel's workgroup has 2048 cells, a tile's at least as many but for
+// meshes it is larger than (8^3: two and four workgroups).
+int64_t reduction_blocks(int n) {
+  const dim3 g = box_grid(Box{{0, 0, 0}, {n - 1, n - 1, n - 1}});
+  int64_t most = (int64_t)g.x * g.y * g.z;
+  for (int ext = 1; ext <= n; ++ext) {
+    const int txv = tile_threads(ext), tx = 4 * txv, ty = 256 / txv;
+    most = std::max(most, (int64_t)((n + tx - 1) / tx) * ((n + ty - 1) / ty) *
+                              ((n + kResKzMin - 1) / kResKzMin));
+  }
+  return most;
+}
+
 template <typename T>
 void launch_residual(const double* phi, const double* rhs, T* r_out, int n, const Box& b,
                      double kappa, double* partial, int* nblocks, hipStream_t st) {
   const int ib = b.lo[0] & ~3;
   prof_begin(st, K_RESIDUAL);
   if (b.hi[0] - ib + 1 >= 64) {
-    // tile width as for the colour sweeps (the extent here in cells, 4 per thread)
-    const int txv = tile_threads(b.hi[0] - ib + 1);
-    const unsigned gx = (unsigned)((b.hi[0] - ib + 4 * txv) / (4 * txv));
-    const unsigned gy = (unsigned)((b.hi[1] - b.lo[1] + 256 / txv) / (256 / txv));
-    const int kz = res_planes(gx * gy, b);
-    const unsigned gz = (unsigned)((b.hi[2] - b.lo[2] + kz) / kz);
-    *nblocks = (int)(gx * gy * gz);
-    const dim3 g(gx * gy * gz), blk(txv, 256 / txv);
+    const auto [txv, kz, blocks] = res_tiles(b);
+    *nblocks = blocks;
+    const dim3 g(blocks), blk(txv, 256 / txv);
     if (txv == 64)
       hipLaunchKernelGGL((k_residual_v4<T, 64>), g, blk, 0, st, phi, rhs, r_out, n, b, kappa,
                          partial, kz);
@@ -2188,16 +2206,10 @@ template <typename T>
 void launch_correct_est(double* phi, const T* e, const T* r_old, float* chg, double pending_scale,
                         double kappa, int n, const Box& b, double* partial, int* nblocks,
                         hipStream_t st) {
-  // the residual's tiles (4 cells per lane; the host asks for this pass only
-  // on boxes at least 16 cells wide, where the narrowest tile fits)
-  const int ib = b.lo[0] & ~3;
-  const int txv = tile_threads(b.hi[0] - ib + 1);
-  const unsigned gx = (unsigned)((b.hi[0] - ib + 4 * txv) / (4 * txv));
-  const unsigned gy = (unsigned)((b.hi[1] - b.lo[1] + 256 / txv) / (256 / txv));
-  const int kz = res_planes(gx * gy, b);
-  const unsigned gz = (unsigned)((b.hi[2] - b.lo[2] + kz) / kz);
-  const dim3 g(gx * gy * gz);
-  *nblocks = (int)g.x;
+  // the residual's tiles (4 cells per lane), on narrow boxes too
+  const auto [txv, kz, blocks] = res_tiles(b);
+  const dim3 g(blocks);
+  *nblocks = blocks;
   prof_begin(st, K_CORRECT_EST);
   if (txv == 64)
     correct_est_tiles<T, 64>(phi, e, r_old, chg, pending_scale, kappa, n, b, partial, g, kz,
@@ -2234,14 +2246,9 @@ bool launch_rhs_residual(const uint64_t* counts, const double* phi, double* rhs,
                          int* nblocks, hipStream_t st, float* g3, double inv2h) {
   const int ib = b.lo[0] & ~3;
   if (b.hi[0] - ib + 1 < 64) return false;
-  const int txv = tile_threads(b.hi[0] - ib + 1);
-  const unsigned gx = (unsigned)((b.hi[0] - ib + 4 * txv) / (4 * txv));
-  const unsigned gy = (unsigned)((b.hi[1] - b.lo[1] + 256 / txv) / (256 / txv));
-  const int kz = res_planes(gx * gy, b);
-  const unsigned gz = (unsigned)((b.hi[2] - b.lo[2] + kz) / kz);
-  const int nb = (int)(gx * gy * gz);
+  const auto [txv, kz, nb] = res_tiles(b);
   *nblocks = nb;
-  const dim3 g(gx * gy * gz), blk(txv, 256 / txv);
+  const dim3 g(nb), blk(txv, 256 / txv);
   const int mode = chg ? (apply ? 2 : 1) : 0;
   const bool force = g3 != nullptr;
   prof_begin(st, force ? K_RHS_FORCE : K_RHS);
