@@ -491,38 +491,34 @@ k_drift_deposit(ParticleArgs pa, double coef, MeshMap mm, unsigned long long* __
 }
 
 // g = sum over the S^3 assignment nodes of w * (-grad Phi) (central
-// differences).  The weights are products of axis weights, so the sum over
-// nodes of w_i (Phi_{i+1} - Phi_{i-1}) along an axis is one over the S + 2
-// potential values around them with the differences d_i = w_{i-1} - w_{i+1}
-// (exact integers): each value of the potential is loaded once, in 8-byte
-// pairs along a row (CIC 32 values in 16 loads instead of 48 loads, TSC 81 in
-// 51 instead of 162), and every row adds to all three components.  The value
-// at the first node is subtracted from each, which keeps the sums' rounding at
-// that of the potential's differences, as in the node by node form.
-// Bound by the gathers: 5 M particles on 256^3, CIC: 148 us (228 node by
-// node); 15.8 M, TSC with kick and drifts: 835 us (1436).
+// differences), node by node: every difference of two potential values is
+// rounded once, whatever their own size, and the nodes add up in order.  The
+// values around the nodes are loaded plane by plane, each of them once, in
+// 8-byte pairs along a row (CIC 32 values in 16 loads instead of 48 loads, TSC
+// 81 in 51 instead of 162).  Bound by the gathers: 5 M particles on 256^3, CIC:
+// 144 us (228 with a load per use); 15.8 M, TSC with kick and drifts: 722 us
+// (1436).  Sums along rows and planes of the values less the first node's took
+// 148 and 829 us, and lost the differences' last digits.
 template <int S>
 __device__ inline void interp_g(const double* __restrict__ phi, const MeshMap& mm,
                                 const Stencil<S>& c, double inv2h, double g[3]) {
   const int n = mm.ng, m = n - 1;
-  double w[3][S], d[3][S + 2];
+  const double norm = ldexp(1.0, -3 * mm.frac_bits);
+  // products of axis weights are integers below 2^53
+  double w[3][S];
 #pragma unroll
-  for (int ax = 0; ax < 3; ++ax) {
+  for (int ax = 0; ax < 3; ++ax)
 #pragma unroll
     for (int t = 0; t < S; ++t) w[ax][t] = (double)c.w[ax][t];
-#pragma unroll
-    for (int t = 0; t < S + 2; ++t)
-      d[ax][t] = (t >= 2 ? w[ax][t >= 2 ? t - 2 : 0] : 0.0) - (t < S ? w[ax][t < S ? t : 0] : 0.0);
-  }
   int jr[S + 2];
 #pragma unroll
   for (int t = 0; t < S + 2; ++t) jr[t] = ((c.cell[1] - 1 + t) & m) * n;
   const int i0 = c.cell[0] - 1;
-  const double ref = phi[lin(c.cell[0] & m, c.cell[1] & m, c.cell[2] & m, n)];
-  double gx = 0.0, gy = 0.0, gz = 0.0;
+  g[0] = g[1] = g[2] = 0.0;
   // rows (j, k) with both in the stencil draw on S + 2 values, those one step
   // outside it along y or z on S
   auto rows = [&](auto load) {
+    double v[3][S + 2][S + 2];                   // plane tz in v[tz % 3]
 #pragma unroll
     for (int tz = 0; tz < S + 2; ++tz) {
       const int64_t plane = (int64_t)((c.cell[2] - 1 + tz) & m) * n * n;
@@ -530,19 +526,21 @@ __device__ inline void interp_g(const double* __restrict__ phi, const MeshMap& m
 #pragma unroll
       for (int ty = 0; ty < S + 2; ++ty) {
         const bool iny = ty > 0 && ty <= S;
-        if (!inz && !iny) continue;
-        double v[S + 2];
-        load(phi + plane + jr[ty], inz && iny, v);
-        double sw = 0.0, sd = 0.0;
+        if (inz || iny) load(phi + plane + jr[ty], inz && iny, v[tz % 3][ty]);
+      }
+      if (tz < 2) continue;
+      // nodes of plane tz - 1
+      const auto &below = v[(tz - 2) % 3], &at = v[(tz - 1) % 3], &above = v[tz % 3];
 #pragma unroll
-        for (int t = 0; t < S; ++t) sw += w[0][t] * (v[t + 1] - ref);
-        if (inz && iny) {
+      for (int y = 1; y <= S; ++y) {
+        const double wyz = w[1][y - 1] * w[2][tz - 2];
 #pragma unroll
-          for (int t = 0; t < S + 2; ++t) sd += d[0][t] * (v[t] - ref);
-          gx += sd * (w[1][iny ? ty - 1 : 0] * w[2][inz ? tz - 1 : 0]);
+        for (int x = 1; x <= S; ++x) {
+          const double wd = w[0][x - 1] * wyz * norm;
+          g[0] += wd * (-(at[y][x + 1] - at[y][x - 1]) * inv2h);
+          g[1] += wd * (-(at[y + 1][x] - at[y - 1][x]) * inv2h);
+          g[2] += wd * (-(above[y][x] - below[y][x]) * inv2h);
         }
-        if (inz) gy += sw * (d[1][ty] * w[2][inz ? tz - 1 : 0]);
-        if (iny) gz += sw * (w[1][iny ? ty - 1 : 0] * d[2][tz]);
       }
     }
   };
@@ -569,10 +567,6 @@ __device__ inline void interp_g(const double* __restrict__ phi, const MeshMap& m
         if (wide || (t > 0 && t <= S)) v[t] = row[(i0 + t) & m];
     });
   }
-  const double norm = -inv2h * ldexp(1.0, -3 * mm.frac_bits);
-  g[0] = gx * norm;
-  g[1] = gy * norm;
-  g[2] = gz * norm;
 }
 
 // The same from the FP32 force mesh g3 (3 values per cell): one 12-byte
