@@ -434,7 +434,7 @@ k_ade_march(double* phi, const double* f, int n, Box b, double lam, uint64_t* ma
         double xq = q < L - 1 ? cen[s][q < L - 1 ? q + 1 : 0] : xn;
         if (lane * L + q == nx - 1) xq = x_after;
         const double s4 = (xq + jp[s][q]) + (un[q] + cen[(s + 1) % D][q]);
-        c[q] = (co * cen[s][q] + lam * (s4 - src[s][q])) * inv;
+        c[q] = s4 - src[s][q];
       }
       // the new row of plane kk - 1
       const int before = w == 0 ? jj % kAdeIn * kRow : kInner + ((w - 1) * kAdeR + jj % kAdeR) * kRow;
@@ -446,8 +446,11 @@ k_ade_march(double* phi, const double* f, int n, Box b, double lam, uint64_t* ma
         if (have > jj) break;
       }
       if (lane == 0) count_set(&taken[w], jj + 1);
+      // one sum and one factor for all of c, as in k_ade_diag: with a factor a of
+      // its own for v a smooth field's error was a third larger at lam = 1000
+      // (co cen, the largest term for small lam, enters unrounded)
 #pragma unroll
-      for (int q = 0; q < L; ++q) c[q] += a * v[q];
+      for (int q = 0; q < L; ++q) c[q] = __builtin_fma(co, cen[s][q], lam * (c[q] + v[q])) * inv;
       if (PER) {
         // the last cell's later x neighbour is the first cell, new by now
         const double u_first = lane_value(c[0] + a * ub, 0);
