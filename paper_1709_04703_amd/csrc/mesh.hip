@@ -2542,6 +2542,22 @@ template void launch_sweeps4<float>(const float*, float*, const float*, int, flo
 template void launch_sweeps4<double>(const double*, double*, const double*, int, double, double, bool,
                                      double*, double, double, const Box*, hipStream_t, const double*);
 
+// t = r - A e on the red cells of box b.
+static void resid_red_v4(const float* e, const float* r, float* t, int n, const Box& b, float inv_scale,
+                         float kappa, hipStream_t st) {
+  const int txv = std::max(16, v4_threads(b));   // rows too short for the 4-cell sweeps too
+  const dim3 g = v4_grid(b, txv);
+  if (txv == 64)
+    hipLaunchKernelGGL((k_resid_red_v4<float, 64>), g, dim3(64, 4), 0, st, e, r, t, n, b, inv_scale,
+                       kappa);
+  else if (txv == 32)
+    hipLaunchKernelGGL((k_resid_red_v4<float, 32>), g, dim3(32, 8), 0, st, e, r, t, n, b, inv_scale,
+                       kappa);
+  else
+    hipLaunchKernelGGL((k_resid_red_v4<float, 16>), g, dim3(16, 16), 0, st, e, r, t, n, b, inv_scale,
+                       kappa);
+}
+
 void launch_separate_sweeps4(const float* e, float* e_out, const float* r, int n, float scale,
                              float inv_diag, bool first, float* t, float inv_scale, float kappa,
                              const Box* box, hipStream_t st) {
@@ -2552,19 +2568,7 @@ void launch_separate_sweeps4(const float* e, float* e_out, const float* r, int n
   L.n = n;
   L.box = b;
   sweep_run<float>(e_out, r, L, 1, 0, 4, first, scale, inv_diag, st);
-  if (t) {
-    const int txv = std::max(16, v4_threads(b));   // rows too short for the 4-cell sweeps too
-    const dim3 g = v4_grid(b, txv);
-    if (txv == 64)
-      hipLaunchKernelGGL((k_resid_red_v4<float, 64>), g, dim3(64, 4), 0, st, e_out, r, t, n, b,
-                         inv_scale, kappa);
-    else if (txv == 32)
-      hipLaunchKernelGGL((k_resid_red_v4<float, 32>), g, dim3(32, 8), 0, st, e_out, r, t, n, b,
-                         inv_scale, kappa);
-    else
-      hipLaunchKernelGGL((k_resid_red_v4<float, 16>), g, dim3(16, 16), 0, st, e_out, r, t, n, b,
-                         inv_scale, kappa);
-  }
+  if (t) resid_red_v4(e_out, r, t, n, b, inv_scale, kappa, st);
 }
 
 // The fused form of pre or post sweeps on level L when it applies (nsweeps ==
@@ -2629,6 +2633,17 @@ static void resid_restrict(const Level& L, const Level& C, T inv_scale, T kappa,
     SDPM_RR(false, 2);
 #undef SDPM_RR
   prof_end(st, K_RESTRICT, sizeof(T) * (1.5 * (double)box_cells(L.box) + (double)box_cells(bc)));
+}
+
+// Whether a level's residual, where the sweeps do not form it, goes through
+// memory: the 4-cell forms of FP32 levels move it at the rate of a copy, which
+// from 2^25 cells on is less than k_resid_restrict's loads take (cycles with
+// one sweep each way, a solve: 512^3 14.2 against 15.0 ms, a box of 383^3 7.47 and
+// 7.70; 256^3 2.46 and 2.44).
+constexpr int64_t kResidApart = (int64_t)1 << 25;
+template <typename T>
+static bool resid_apart(const Level& L) {
+  return sizeof(T) == 4 && v4_threads(L.box) && box_cells(L.box) >= kResidApart;
 }
 
 // r_C = restriction of L's red residual t; the vector form for FP32 levels
@@ -2760,9 +2775,15 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
         sweeps4<T>(L, l, periodic, pre, zero, scale, inv_diag, st, post > 0, inv_scale, (T)kappa);
     if (fused == kNotFused) sweep_run<T>((T*)L.e, r, L, l, 0, 2 * pre, zero, scale, inv_diag, st);
     const Level& C = lv[l + 1];
-    if (fused != kDone) {
+    if (fused != kDone && !resid_apart<T>(L)) {
       resid_restrict<T>(L, C, inv_scale, (T)kappa, st);
       continue;
+    }
+    if (fused != kDone) {
+      prof_begin(st, K_RESID_LEVEL);
+      resid_red_v4((const float*)L.e, (const float*)r, (float*)L.t, L.n, L.box, (float)inv_scale,
+                   (float)kappa, st);
+      prof_end(st, K_RESID_LEVEL, 2.0 * es * cells);
     }
     prof_begin(st, K_RESTRICT);
     restrict_level<T>(L, C, st);

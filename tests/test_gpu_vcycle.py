@@ -83,3 +83,29 @@ def test_one_cycle(ng, levels, pre, post, kappa, prec):
 @pytest.mark.parametrize("prec", [0, 1])
 def test_one_cycle_without_post_smoothing(ng, levels, prec):
     test_one_cycle(ng, levels, 2, 0, 1e-4, prec)
+
+
+# From 2^25 cells on, FP32 levels outside V(2,2) form the residual apart from
+# its restriction: the same cycle, so it converges as on the next smaller mesh,
+# whose residual is restricted as it is formed.
+@pytest.mark.parametrize("pre,post", [(1, 1), (3, 3), (2, 0)])
+def test_cycles_do_not_depend_on_the_mesh(pre, post):
+    import torch
+
+    kappa, tol, cycles = 0.05, 1e-7, []
+    for ng in (256, 512):
+        box, n = 100.0, 3000
+        x, p, ids = uniform_particles(n, box, 1)
+        cfg = lib_config(ng, box, precision=0, tol=tol, n_initial=n, pre=pre, post=post)
+        sim = make_sim(cfg, n)
+        sim.bind(x, p, ids)
+        sim.deposit()
+        cycles.append(sim.solve(kappa, 1.0)["vcycles"])
+        phi = sim.phi
+        lap = sum(torch.roll(phi, s, d) for d in range(3) for s in (1, -1)) - 6.0 * phi
+        res = (lap.sub_(phi, alpha=kappa)).sub_(sim.rhs)
+        assert float(res.norm()) <= 1.01 * tol * float(sim.rhs.norm())
+        sim.close()
+        del sim, phi, lap, res
+        torch.cuda.empty_cache()
+    assert cycles[1] <= cycles[0] + 1
