@@ -344,8 +344,9 @@ int sdpm_solve(sdpm_ctx* ctx, double kappa_h2, double s_h2_factor, sdpm_step_sta
  * periodic; frozen exterior otherwise.  lam = D dt / h^2 > 0 (sdpm_step uses
  * 1 / kappa_h2 of the half sub-step).  Runs on the context's stream in a
  * clearing launch and one for the sweep; boxes with rows of more than 512
- * cells take one launch per diagonal of rows (ny + nz - 1 launches).
- * SDPM_EINVAL for lam not finite and positive.                              */
+ * cells take one launch per diagonal of rows (ny + nz - 1 launches).  Rows
+ * pass between workgroups through the workspace's residual array, which the
+ * next solve forms anew.  SDPM_EINVAL for lam not finite and positive.                              */
 int sdpm_ade_sweep(sdpm_ctx* ctx, double lam, int forward);
 /* The multigrid smoother of the implicit solve (Sec. 2.1 Eq. 4) on one
  * periodic FP32 level: four red-black Gauss-Seidel half sweeps (red, black,
@@ -522,7 +523,9 @@ int sdpm_profile_kernels(sdpm_ctx* ctx, const char* names);
  * Totals cover launches completed by the last synchronising call.  On levels
  * whose passes are one launch each way, that launch counts as the half sweeps
  * in it ("smooth_color" on the finest level, else "smooth_color_coarse"), with
- * the bytes of as many separate ones.                                      */
+ * the bytes of as many separate ones.  "resid_red" is the residual of levels
+ * that form it in a launch of its own; a residual formed by the pass that
+ * restricts it counts there ("restrict_fw").                                */
 int sdpm_profile_read(sdpm_ctx* ctx, sdpm_kernel_stat* out, int32_t max, int32_t* n);
 
 int sdpm_destroy(sdpm_ctx* ctx);

@@ -876,11 +876,11 @@ k_smooth_color_v4(T* __restrict__ eo, const T* __restrict__ ex, const T* __restr
   }
 }
 
-// Four colour sweeps (red, black, red, black) of a level in one pass, with the
-// arithmetic of four k_smooth_color_v4 (in FP64 k_smooth_color) launches (same
-// operands, same order: bit-identical results).  The figures are of FP32 levels
-// unless they say otherwise.  Four separate sweeps move
-// 24 bytes per cell (each half sweep reads the other colour and its own r,
+// Four colour sweeps (red, black, red, black) of a level in one pass, each cell
+// with the operands of a k_smooth_color_v4 (in FP64 k_smooth_color) launch in
+// the same order (the bits of four such launches, which the tests of FP32
+// levels ask for).  The figures are of FP32 levels unless they say otherwise.
+// Four separate sweeps move 24 bytes per cell (each half sweep reads the other colour and its own r,
 // writes its own colour); here each cell's r and input black value are read
 // once and its final red and black values written once: 10 bytes per cell
 // (8 with the zero initial guess, which reads no e).
@@ -928,7 +928,7 @@ k_smooth_color_v4(T* __restrict__ eo, const T* __restrict__ ex, const T* __restr
 // level's prolonged correction on the way in, which saves the pass that reads
 // and writes them for it: 512^3 423 -> 334 us for both, 256^3 61 -> 52, 128^3
 // 19.2 -> 16.7 (with the loads of the coarse rows in every step, not every
-// other: 386, 61 and 19.7).
+// other: 386, 61 and 19.7).  In the order of k_prolong_black_v4, in FP64 too.
 //
 // Requires n a power of two >= 8 UX, n % zc == 0.  FIRST: the red sweep starts
 // from e = 0 and ein is not read (eout may be the level's e); otherwise ein
@@ -1241,7 +1241,8 @@ k_sweep4(const T* __restrict__ ein, T* __restrict__ eout, const T* __restrict__ 
   }
 }
 
-// k_resid_red with 4 red cells per thread (see k_smooth_color_v4).
+// t = r - A_l e on the red cells of the box, 4 per thread (see
+// k_smooth_color_v4), after a sweep that ended black.
 template <typename T, int TXV>
 __global__ void __launch_bounds__(256)
 k_resid_red_v4(const T* __restrict__ e, const T* __restrict__ r, T* __restrict__ tout, int n, Box b,
@@ -1295,34 +1296,6 @@ k_resid_red_v4(const T* __restrict__ e, const T* __restrict__ r, T* __restrict__
   }
 }
 
-// Full weighting: r_c(I) = sum_{o in {-1,0,1}^3} w(o) t_f(2I + o),
-// w = (1/4, 1/2, 1/4) per axis.  Only red fine cells (o_x + o_y + o_z even)
-// carry a residual.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_restrict(const T* __restrict__ tf, T* __restrict__ rc, int nf, int nc, Box bc) {
-  const Tile tl = tile_box(bc);
-  const int I = bc.lo[0] + tl.bx * kBoxTx + threadIdx.x;
-  const int J = bc.lo[1] + tl.by * kBoxTy + threadIdx.y;
-  if (I > bc.hi[0] || J > bc.hi[1]) return;
-  const int m = nf - 1;
-  const int K0 = bc.lo[2] + tl.bz * kBoxKz;
-  const int K1 = min(K0 + kBoxKz - 1, bc.hi[2]);
-  const int hn = nf >> 1;
-  for (int K = K0; K <= K1; ++K) {
-    // red fine cells of the 3x3x3 stencil, grouped by weight
-    const int i = 2 * I, j = 2 * J, k = 2 * K;
-    const int im = (i - 1) & m, ip = (i + 1) & m, jm = (j - 1) & m, jp = (j + 1) & m;
-    const int km = (k - 1) & m, kp = (k + 1) & m;
-    auto R = [&](int x, int y, int z) -> T { return tf[((int64_t)z * nf + y) * hn + (x >> 1)]; };
-    const T centre = R(i, j, k);
-    const T edges = R(im, jm, k) + R(ip, jm, k) + R(im, jp, k) + R(ip, jp, k) +
-                    R(im, j, km) + R(ip, j, km) + R(im, j, kp) + R(ip, j, kp) +
-                    R(i, jm, km) + R(i, jp, km) + R(i, jm, kp) + R(i, jp, kp);
-    rc[sidx(I, J, K, nc)] = (T)0.125 * centre + (T)0.03125 * edges;
-  }
-}
-
 // Prolongation and correction of the black cells only: the next sweep starts
 // with the red colour, whose update reads only black neighbours and
 // overwrites the red values, so red cells need no correction.  Threads map
@@ -1370,14 +1343,15 @@ k_prolong(const T* __restrict__ ec, T* __restrict__ ef, int nc, int nf, Box bf, 
   }
 }
 
-// The residual r - A_l e of a level restricted onto the next.  After a sweep
-// that ends with the black colour the black residual is zero (each black
-// equation was just solved exactly), so only the red cells of k_restrict's
-// stencil count.  A workgroup takes kRrX x kRrY x CZ coarse cells: the red
-// residuals under them (and one cell around, computed by the neighbours too)
-// go to LDS and are weighted there, so that the residual neither goes to memory
-// nor comes back.  Same arithmetic as a residual in memory and its restriction;
-// V4: in the order of k_restrict_v4.
+// The residual r - A_l e of a level restricted onto the next by full weighting:
+// r_c(I) = sum_{o in {-1,0,1}^3} w(o) t(2I + o), w = (1/4, 1/2, 1/4) per axis.
+// After a sweep that ends with the black colour the black residual is zero
+// (each black equation was just solved exactly), so only the red cells of the
+// stencil (o_x + o_y + o_z even) count.  A workgroup takes kRrX x kRrY x CZ
+// coarse cells: the red residuals under them (and one cell around, computed by
+// the neighbours too) go to LDS and are weighted there, so that the residual
+// neither goes to memory nor comes back.  The operations of a residual in memory
+// and its restriction; V4: in the order of k_restrict_v4.
 // Bound by the loads, eight a residual, from the caches: 256^3 in FP64 67 us
 // with CZ = 8 (59 + 21 in two launches; 73 with CZ = 4); 128^3, where a
 // workgroup's own chain of loads counts, with CZ = 2 11.0 us (10.4 + 6.5; 12.2
@@ -1467,7 +1441,7 @@ k_resid_restrict(const T* __restrict__ e, const T* __restrict__ r, T* __restrict
 // 4 and 2 (the host takes them for fine boxes of at least 64 cells a row).
 //
 // Restriction of 4 coarse cells I0 .. I0 + 3 (I0 a multiple of 4): the red
-// fine cells of k_restrict's stencil lie at half index I in the rows whose
+// fine cells of the stencil lie at half index I in the rows whose
 // offsets (o_y, o_z) are both even or both odd (the centre and the four
 // diagonal rows) and at half indices I - 1 and I in the other four rows, so
 // each fine row is one vector (plus the value before it).  The coarse cells
@@ -1820,6 +1794,8 @@ k_coarse_modes(double* __restrict__ e, const double* __restrict__ r, double scal
   }
 }
 
+// Residual of phi + scale * d, with d applied only inside the box (the
+// learned initial guess); written colour-split like k_residual.
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_residual_guess(const double* __restrict__ phi, const float* __restrict__ d, double scale,
@@ -2472,8 +2448,8 @@ template <typename T>
 void launch_sweeps4(const T* e, T* e_out, const T* r, int n, T scale, T inv_diag, bool first, T* t,
                     T inv_scale, T kappa, const Box* box, hipStream_t st, const T* coarse) {
   const Box b = box ? *box : whole_mesh(n);
-  // 128 x 32-cell columns (one 768-thread workgroup per compute unit: 138
-  // KB of LDS, 160 KB with the residual); 64 x 32 on a 64^3 mesh
+  // 128 x 32-cell columns take one 768-thread workgroup per compute unit (138
+  // KB of LDS, 160 KB with the residual).
   // 128-cell columns on periodic levels of 256^3 and up and on boxes in
   // meshes of 512^3 and up; 64-cell columns (two workgroups per CU) on
   // smaller meshes and on the boxes of the 256^3 level, where the chunks
@@ -2576,7 +2552,8 @@ void launch_separate_sweeps4(const float* e, float* e_out, const float* r, int n
 // guess it writes e, else it reads e and writes a second array, and the two
 // swap: e_alt, or where the level has none t, the residual's scratch, which is
 // free then and like them zero outside the box.  Says what it did: kDone with
-// the red residual in t (on request, with an e_alt), kSwept without.
+// the red residual in t (on request, with an e_alt and rows long enough for its
+// restriction), kSwept without.
 enum Sweeps4 { kNotFused, kSwept, kDone };
 template <typename T>
 static Sweeps4 sweeps4(Level& L, int level, bool periodic, int nsweeps, bool zero, T scale, T inv_diag,
@@ -2586,7 +2563,7 @@ static Sweeps4 sweeps4(Level& L, int level, bool periodic, int nsweeps, bool zer
   bool whole = true;
   for (int d = 0; d < 3; ++d) whole = whole && L.box.lo[d] == fb.lo[d] && L.box.hi[d] == fb.hi[d];
   void*& alt = L.e_alt ? L.e_alt : L.t;
-  resid = resid && L.e_alt;
+  resid = resid && L.e_alt && v4_threads(L.box);
   // a frozen-exterior box (which keeps a plane from every face) with at
   // least 128^3 cells; periodic levels are whole
   if (nsweeps != 2 || L.n < kSweep4Min || (periodic && !whole) ||
@@ -2646,32 +2623,23 @@ static bool resid_apart(const Level& L) {
   return sizeof(T) == 4 && v4_threads(L.box) && box_cells(L.box) >= kResidApart;
 }
 
-// r_C = restriction of L's red residual t; the vector form for FP32 levels
-// whose fine box takes the vector sweeps.
-template <typename T>
-static void restrict_level(const Level& L, const Level& C, hipStream_t st) {
+// r_C = restriction of L's red residual t, where the 4-cell forms apply to L.
+static void restrict_red(const Level& L, const Level& C, hipStream_t st) {
   const Box& bc = C.box;
-  if constexpr (sizeof(T) == 4) {
-    if (v4_threads(L.box)) {
-      const int txv = tile_threads(bc.hi[0] - (bc.lo[0] & ~3) + 1);
-      const int ty = 256 / txv;
-      const unsigned gx = (unsigned)((bc.hi[0] - (bc.lo[0] & ~3) + 4 * txv) / (4 * txv));
-      const unsigned gy = (unsigned)((bc.hi[1] - bc.lo[1] + ty) / ty);
-      const unsigned gz = (unsigned)((bc.hi[2] - bc.lo[2] + kVecKz) / kVecKz);
-      const dim3 g(gx * gy * gz), blk(txv, ty);
-      const float* t = (const float*)L.t;
-      float* r = (float*)C.r;
-      if (txv == 64)
-        hipLaunchKernelGGL(k_restrict_v4<64>, g, blk, 0, st, t, r, L.n, C.n, bc);
-      else if (txv == 32)
-        hipLaunchKernelGGL(k_restrict_v4<32>, g, blk, 0, st, t, r, L.n, C.n, bc);
-      else
-        hipLaunchKernelGGL(k_restrict_v4<16>, g, blk, 0, st, t, r, L.n, C.n, bc);
-      return;
-    }
-  }
-  hipLaunchKernelGGL(k_restrict<T>, box_grid(bc), dim3(kBoxTx, kBoxTy), 0, st, (const T*)L.t,
-                     (T*)C.r, L.n, C.n, bc);
+  const int txv = tile_threads(bc.hi[0] - (bc.lo[0] & ~3) + 1);
+  const int ty = 256 / txv;
+  const unsigned gx = (unsigned)((bc.hi[0] - (bc.lo[0] & ~3) + 4 * txv) / (4 * txv));
+  const unsigned gy = (unsigned)((bc.hi[1] - bc.lo[1] + ty) / ty);
+  const unsigned gz = (unsigned)((bc.hi[2] - bc.lo[2] + kVecKz) / kVecKz);
+  const dim3 g(gx * gy * gz), blk(txv, ty);
+  const float* t = (const float*)L.t;
+  float* r = (float*)C.r;
+  if (txv == 64)
+    hipLaunchKernelGGL(k_restrict_v4<64>, g, blk, 0, st, t, r, L.n, C.n, bc);
+  else if (txv == 32)
+    hipLaunchKernelGGL(k_restrict_v4<32>, g, blk, 0, st, t, r, L.n, C.n, bc);
+  else
+    hipLaunchKernelGGL(k_restrict_v4<16>, g, blk, 0, st, t, r, L.n, C.n, bc);
 }
 
 // e_L += prolongation of e_C on L's black cells (all cells with all_cells);
@@ -2786,7 +2754,7 @@ const T* vcycle(Level* lv, int nlev_all, double kappa, int pre, int post, int co
       prof_end(st, K_RESID_LEVEL, 2.0 * es * cells);
     }
     prof_begin(st, K_RESTRICT);
-    restrict_level<T>(L, C, st);
+    restrict_red(L, C, st);
     prof_end(st, K_RESTRICT, es * (cells / 2 + (double)box_cells(C.box)));
   }
   {
