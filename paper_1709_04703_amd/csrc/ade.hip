@@ -33,8 +33,8 @@
 // fill an XCD with waiting workgroups of which each sweep's next one needs a
 // compute unit there).  The sweep takes about ny + nz
 // steps of one row and the mail's way (about 4 us) per workgroup, instead of
-// ny + nz - 1 dependent launches: 0.18 ms per sweep at 128^3, 0.59 at 256^3,
-// 2.97 at 512^3, against 1.1, 2.2 and 8.5 ms.  (Barriers per row and the rows
+// ny + nz - 1 dependent launches: 0.18 ms per sweep at 128^3, 0.60 at 256^3,
+// 3.02 at 512^3, against 0.83, 2.12 and 8.33 ms.  (Barriers per row and the rows
 // published by release and acquire fences: 0.32, 1.06 and 4.4 ms; fetching
 // four rows of mail at a time instead of two: 0.65 ms at 256^3.)
 //
@@ -541,7 +541,11 @@ void launch_ade_sweep(double* phi, const double* f, int n, const Box& b, bool pe
   const int per = periodic ? 1 : 0;
   prof_begin(st, K_ADE);
   // T planes per workgroup (with the input and the output wave 8 waves, two per
-  // SIMD, 256 registers each) and D rows of prefetch, as many as these take
+  // SIMD, 256 registers each) and D rows of prefetch, as many as these take on
+  // the periodic mesh.  In a box, where every cell has an index of its own, rows
+  // of more than 128 cells spill (6 registers, 45 of more than 256 cells): boxes
+  // of 108^3, 210^3 and 466^3 take 0.15, 0.59 and 4.9 ms (by diagonals 0.70,
+  // 1.65 and 7.1)
   if (nx <= 64)
     ade_march<1, 6, 6>(phi, f, n, b, per, lam, forward, (uint64_t*)scratch, ticket, st);
   else if (nx <= 128)

@@ -4,11 +4,10 @@
 //
 // Each layer is an implicit GEMM over taps t:  Out^T (16 co x voxels) +=
 // W_t^T (16 co x 16 ci) * In_t^T (16 ci x voxels).  Activations are stored
-// channels-last (16 BF16 = 32 B per voxel), so a lane's B fragment (8 or 4
-// channels of one voxel) is one 16- or 8-byte read and its D fragment (4
-// channels of one voxel) one 8-byte write.  MFMA lane layouts (64 lanes,
-// g = lane / 16, r = lane % 16): 16x16x16 A[r][4g..4g+3], B[4g..4g+3][r];
-// 16x16x32 A[r][8g..8g+7], B[8g..8g+7][r]; both D[4g..4g+3][r].
+// channels-last (16 BF16 = 32 B per voxel), so a lane's B fragment (8
+// channels of one voxel) is one 16-byte read and its D fragment (4 channels of
+// one voxel) one 8-byte write.  MFMA lane layout (64 lanes, g = lane / 16, r =
+// lane % 16), 16x16x32: A[r][8g..8g+7], B[8g..8g+7][r], D[4g..4g+3][r].
 //
 // The data gradient of a layer is the same kernel with the taps mirrored and
 // the channel roles swapped (BACKWARD flag); the weight gradient reduces
@@ -66,10 +65,15 @@ __device__ inline int64_t vox(int i, int j, int k, int n) { return ((int64_t)k *
 // weights stay in registers.  A tap's contributions are added plane by plane
 // and row by row, as in a block of planes held at once, so results do not
 // depend on zc.
-// Bound by HBM and L2 (64 bytes per voxel and the halos; 96 with the mask)
-// once two workgroups share a CU: 128^3 takes 57 us forward and 69 us backward
-// with the mask, 256^3 346 and 428 us (blocks of 4 planes loaded between
-// barriers, one workgroup per CU at 128^3: 96, 120, 552 and 705 us).
+// 128^3 takes 57 us forward and 69 us backward with the mask, 256^3 346 and 428
+// us (blocks of 4 planes loaded between barriers, one workgroup per CU at 128^3:
+// 96, 120, 552 and 705 us).  Neither HBM nor LDS bounds it (counters at 128^3:
+// 107 MB, 2.3 TB/s, half a copy's rate; LDS active 9 % of the time, no bank
+// conflicts): the matrix cores are busy 41 % of the time, a quarter of it on the
+// second fragment's zero half, other vector instructions issue for about 28 %,
+// and a wave waits for memory or a barrier for 36 %.  With the mask the waits
+// are 56 %, the matrix cores 28 %.  252 registers, two waves per SIMD; with the
+// mask 215 for 4 rows, and 256 with 58 spilled for 8.
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int kBX = 64 + 2;
 
