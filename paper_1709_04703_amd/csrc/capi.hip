@@ -240,7 +240,7 @@ size_t carve(const sdpm_config& c, int64_t capacity, char* base, sdpm_ctx* ctx) 
                                         : nullptr;
   if (c.solver == SDPM_SOLVER_FFT) {
     // the padded half spectrum and the root table, the symbol table
-    void* buf = take(fft_buffer_bytes(c.ng));
+    void* buf = take(2 * fft_complex_bytes(c.ng));
     double* sym = (double*)take((size_t)c.ng * sizeof(double));
     if (ctx) {
       ctx->fft.c = buf;

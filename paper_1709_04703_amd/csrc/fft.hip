@@ -331,10 +331,8 @@ int fft_pitch(int n) { return n >= 32 ? n / 2 + 8 : n / 2 + 1; }
 
 size_t fft_complex_bytes(int n) { return (size_t)n * n * (n / 2 + 1) * sizeof(c64); }
 
-// At most 2 fft_complex_bytes(n), which the power spectrum reserves: the padding
-// takes at most 7 of n / 2 + 1 further columns and the table one row.
-size_t fft_buffer_bytes(int n) { return ((size_t)n * n * fft_pitch(n) + n) * sizeof(c64); }
-
+// Fits 2 fft_complex_bytes(n), the size the layouts reserve: the padding takes
+// at most 7 of n / 2 + 1 further columns and the table one row.
 int fft_init(FftPlan* p, int n, void* buf, double* sym_dev, hipStream_t st) {
   p->n = n;
   p->pitch = fft_pitch(n);

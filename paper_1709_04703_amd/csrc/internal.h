@@ -177,8 +177,8 @@ void launch_reduce_final(const double* partial, int nblocks, int nslots, double*
                          hipStream_t st);
 // Exact periodic FFT solve of (Lap_h - kappa h^2) phi = rhs (fft.hip) on an
 // n^3 mesh: the half spectrum c (rows of `pitch` complex values, the first n
-// / 2 + 1 used) and the root table tw share a buffer of fft_buffer_bytes(n)
-// (at most 2 fft_complex_bytes(n)), sym is the 1-D symbol table (n values).
+// / 2 + 1 used) and the root table tw share a buffer of 2
+// fft_complex_bytes(n), sym is the 1-D symbol table (n values).
 struct FftPlan {
   int n = 0;
   int pitch = 0;
@@ -187,7 +187,6 @@ struct FftPlan {
   double* sym = nullptr;
 };
 size_t fft_complex_bytes(int n);
-size_t fft_buffer_bytes(int n);
 // Sets up p and enqueues the tables' computation.  This and the transforms
 // return SDPM_EHIP when a launch of theirs fails, SDPM_EINVAL for other sizes.
 int fft_init(FftPlan* p, int n, void* buf, double* sym_dev, hipStream_t st);

@@ -1,7 +1,5 @@
-"""What the workspace holds.  A partial sum for every workgroup of every
-reduction: the tiles of the residual passes over any box of the mesh, and the
-box kernels'.  For the FFT solver one half spectrum, which it transforms in
-place."""
+"""The workspace holds a partial sum for every workgroup of every reduction: the
+tiles of the residual passes over any box of the mesh, and the box kernels'."""
 from __future__ import annotations
 
 import ctypes
@@ -38,14 +36,3 @@ def test_partials_of_every_box(n):
     for x in xs:
         for y, z in itertools.product(spans, spans):
             assert tiles((x[0], 0, 0), (x[1], y - 1, z - 1)) <= reserved(n)
-
-
-@pytest.mark.parametrize("ng", [8, 64, 512, 2048])
-def test_fft_solver_holds_one_spectrum(ng):
-    cfg = P.config_default(ng, 100.0)
-    plain = P.workspace_bytes(cfg, 1)
-    cfg.solver = P.SDPM_SOLVER_FFT
-    # rows of n / 2 + 1 values padded by at most 7, a root table, a symbol
-    # table, each rounded up to 256 bytes
-    most = ng * ng * (ng // 2 + 8) * 16 + ng * 16 + 256 + ng * 8 + 256
-    assert 0 < P.workspace_bytes(cfg, 1) - plain <= most
