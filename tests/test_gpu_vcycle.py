@@ -109,3 +109,84 @@ def test_cycles_do_not_depend_on_the_mesh(pre, post):
         del sim, phi, lap, res
         torch.cuda.empty_cache()
     assert cycles[1] <= cycles[0] + 1
+
+
+def _box_vcycle(r, kappa, level, boxes, pre, post, coarse_sweeps):
+    """The cycle on a frozen-exterior box: boxes[l] = (lo, hi) in (x, y, z) of
+    level l, everything 0 outside them."""
+    def inside(n, box):
+        m = np.zeros((n, n, n), dtype=bool)
+        m[tuple(slice(box[0][d], box[1][d] + 1) for d in (2, 1, 0))] = True
+        return m
+
+    def sweeps(e, count):
+        for _ in range(count):
+            for colour in (0, 1):
+                e = np.where(box & (parity == colour),
+                             (_neighbours(e) - scale * r) / (6.0 + scale * kappa), e)
+        return e
+
+    n, scale = r.shape[0], 4.0**level
+    box, parity = inside(n, boxes[level]), np.indices(r.shape).sum(0) & 1
+    e = np.zeros_like(r)
+    if level == len(boxes) - 1:
+        return sweeps(e, min(coarse_sweeps, _sweeps_for_1e3(boxes[level], level, kappa)))
+    e = sweeps(e, pre)
+    t = np.where(box, r - (_neighbours(e) - 6.0 * e) / scale + kappa * e, 0.0)
+    for ax in range(3):
+        t = 0.5 * t + 0.25 * (np.roll(t, 1, ax) + np.roll(t, -1, ax))
+    c = _box_vcycle(t[::2, ::2, ::2], kappa, level + 1, boxes, pre, post, coarse_sweeps)
+    for ax in range(3):
+        c = np.stack([c, 0.5 * (c + np.roll(c, -1, ax))], ax + 1)
+        c = c.reshape(c.shape[:ax] + (-1,) + c.shape[ax + 2:])
+    return sweeps(np.where(box, e + c, 0.0), post)
+
+
+def _sweeps_for_1e3(box, level, kappa):
+    rho = (sum(2.0 * np.cos(np.pi / (hi - lo + 2)) for lo, hi in zip(*box)) /
+           (6.0 + 4.0**level * kappa))
+    return max(1, int(np.ceil(np.log(1e-3) / (2.0 * np.log(rho)))))
+
+
+# boxes whose faces lie anywhere in the tiles, columns and vectors of the passes
+@pytest.mark.parametrize("ng,levels,radius,pre,post",
+                         [(ng, levels, radius, pre, post)
+                          for ng, levels, radii in ((32, 3, (6.2, 9.7)), (64, 4, (9.4, 22.6)),
+                                                    (128, 5, (30.3, 53.8)))
+                          for radius in radii for pre, post in ((2, 2), (1, 1), (3, 2), (2, 0))] +
+                         [(256, 5, 90.7, 2, 2), (256, 5, 101.2, 2, 1)])
+@pytest.mark.parametrize("kappa", [0.02, 0.4])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_one_cycle_on_a_box(ng, levels, radius, pre, post, kappa, prec):
+    box, n = 10.0 * ng, 3000
+    rng = np.random.default_rng(ng)
+    # off the mesh's centre, so that the faces differ from axis to axis
+    obs = (0.5 * box + 4.0, 0.5 * box - 13.0, 0.5 * box + 21.0)
+    x = np.array(obs) + rng.uniform(-20.0, 20.0, size=(n, 3))
+    cfg = lib_config(ng, box, c_grav=-1.0, shrink=1, precision=prec, tol=0.99, n_initial=n,
+                     mg_levels=levels, pre=pre, post=post, cycles_per_outer=1, box_align=1, x_obs=obs)
+    sim = make_sim(cfg, n)
+    sim.bind(x, np.zeros((n, 3)), np.arange(n))
+    sim.shrink_radius(radius * box / ng)
+    st = sim.state()
+    assert st["periodic"] == 0
+    # the levels' boxes, down to the first that its own sweeps solve
+    boxes = [(list(st["lo"]), list(st["hi"]))]
+    for level in range(1, levels):
+        lo, hi = boxes[-1]
+        lo, hi = [(v + 1) >> 1 for v in lo], [min(v >> 1, (ng >> level) - 2) for v in hi]
+        if any(b < a for a, b in zip(lo, hi)):
+            break
+        boxes.append((lo, hi))
+        if level < levels - 1 and _sweeps_for_1e3(boxes[-1], level, kappa) <= pre + post + 1:
+            break
+    sim.deposit()
+    assert sim.solve(kappa, 1.0)["vcycles"] == 1
+    got, rhs = sim.phi_numpy(), np.zeros((ng,) * 3)
+    sl = tuple(slice(st["lo"][d], st["hi"][d] + 1) for d in (2, 1, 0))
+    rhs[sl] = sim.rhs.cpu().numpy()[sl]
+    want = _box_vcycle(rhs, kappa, 0, boxes, pre, post, cfg.coarse_sweeps)
+    eps = 2.0**-24 if prec == 0 else 2.0**-53
+    tol = 16 * (cfg.coarse_sweeps + levels * (pre + post)) * eps * np.abs(want).max()
+    assert np.abs(got - want).max() <= tol
+    sim.close()
