@@ -922,7 +922,8 @@ k_smooth_color_v4(T* __restrict__ eo, const T* __restrict__ ex, const T* __restr
 // FP64: an LDS plane is twice as large, which leaves room for 64 x 32-cell
 // columns without the residual's stage (154 KB).  256^3: 97 us per pass, 76
 // from zero, against 172 and 154 in separate sweeps (which move 48 bytes a cell
-// at the rate of a copy); FP64 step on 256^3 with TSC 5.53 -> 4.51 ms.
+// at the rate of a copy); FP64 step on 256^3 with TSC 5.53 -> 4.51 ms.  256
+// registers at most; the box form with the prolongation spills 8 more.
 //
 // PROL (post-smoothing): the input black values are corrected by the next
 // level's prolonged correction on the way in, which saves the pass that reads
